@@ -172,8 +172,7 @@ struct pg_plan_s {
     std::vector<int64_t> h_tiles, h_seg;
     // dense
     DenseView dense;
-    int dense_groups = 0;
-    bool dense_fused = false;
+    DenseCfg dense_cfg;
     // the section 4 example
     int64_t lap_n = 0;
     bool lap_atomic = false;
@@ -409,15 +408,13 @@ void layout_batch(pg_plan_s* p) {
 void layout_dense(pg_plan_s* p) {
     Layout L;
     const DenseView& d = p->dense;
-    const int64_t vn = p->dtype == PG_F64 ? 2 : 4;
-    p->dense_fused = d.cols <= dense_fused_max_cols() * (p->dtype == PG_F64 ? 1 : 2) && d.cols % vn == 0;
-    p->dense_groups = (int)std::max<int64_t>(1, std::min<int64_t>(d.rows, 256));
-    p->n_partials = (size_t)std::max<int64_t>(std::max<int64_t>(d.rows, p->dense_groups), 1);
+    p->dense_cfg = dense_config(d);
+    const DenseCfg& c = p->dense_cfg;
+    p->n_partials = (size_t)std::max(c.bands, c.row_groups);
     p->o_partials = L.take(sizeof(double) * p->n_partials);
     p->o_flag = L.take(sizeof(int32_t) * 4);
-    p->o_v = L.take(sizeof(double) * (size_t)std::max<int64_t>(d.rows, 1));
-    if (p->dense_fused)
-        p->o_colpart = L.take(sizeof(double) * (size_t)p->dense_groups * (size_t)d.cols);
+    if (!c.fused) p->o_v = L.take(sizeof(double) * (size_t)std::max<int64_t>(d.rows, 1));
+    p->o_colpart = L.take(sizeof(double) * (size_t)c.bands * (size_t)d.cols);
     p->ws_bytes = L.total;
 }
 
@@ -1212,23 +1209,32 @@ pg_status dense_run(pg_plan p, const void* x, const double* fbar, void* grad, do
         if (f_out && obj) PG_HIP(launch_final_sum(partials, 0, f_out, s));
         return PG_OK;
     }
-    // The fused kernel reads x with 16-byte vector loads.
-    if (p->dense_fused && ((uintptr_t)x % 16) == 0) {
+    const DenseCfg& c = p->dense_cfg;
+    double* colpart = p->at<double>(p->o_colpart);
+    if (!grd) {
+        // f alone: the team form while a row fits one wave, else the row
+        // pass, which holds no column sums.
         PG_HIP(tkern(p, true));
-        PG_HIP(launch_dense_fused(d, x, fbar, grd ? 1 : 0, partials, p->at<double>(p->o_colpart),
-                                  p->dense_groups, s));
+        if (c.fused && c.nw == 1)
+            PG_HIP(launch_dense_fused(d, c, x, fbar, 0, partials, nullptr, s));
+        else
+            PG_HIP(launch_dense_rows(d, c, x, fbar, partials, nullptr, s));
         PG_HIP(tkern(p, false));
-        if (grd)
-            PG_HIP(launch_dense_colsum(p->at<double>(p->o_colpart), p->dense_groups, d.cols, grad,
-                                       dt, p->opt.accumulate, s));
-        if (f_out && obj) PG_HIP(launch_final_sum(partials, p->dense_groups, f_out, s));
+        if (f_out) PG_HIP(launch_final_sum(partials, c.fused && c.nw == 1 ? c.bands : c.row_groups, f_out, s));
+    } else if (c.fused) {
+        PG_HIP(tkern(p, true));
+        PG_HIP(launch_dense_fused(d, c, x, fbar, 1, partials, colpart, s));
+        PG_HIP(tkern(p, false));
+        PG_HIP(launch_dense_colsum(colpart, c.bands, d.cols, grad, dt, p->opt.accumulate, partials,
+                                   c.bands, obj ? f_out : nullptr, s));
     } else {
-        double* v = grd ? p->at<double>(p->o_v) : nullptr;
+        double* v = p->at<double>(p->o_v);
         PG_HIP(tmark(p, 1, true, s));
-        PG_HIP(launch_dense_rows(d, x, fbar, partials, v, s));
+        PG_HIP(launch_dense_rows(d, c, x, fbar, partials, v, s));
+        PG_HIP(launch_dense_cols(d, c, v, colpart, s));
         PG_HIP(tmark(p, 1, false, s));
-        if (grd) PG_HIP(launch_dense_cols(d, v, grad, p->opt.accumulate, s));
-        if (f_out && obj) PG_HIP(launch_final_sum(partials, d.rows, f_out, s));
+        PG_HIP(launch_dense_colsum(colpart, c.bands, d.cols, grad, dt, p->opt.accumulate, partials,
+                                   c.row_groups, obj ? f_out : nullptr, s));
     }
     return PG_OK;
 }

@@ -273,22 +273,34 @@ struct DenseView {
     const void* w = nullptr;
 };
 
-// Fused single pass over A: per row r_i = A_i . x (workgroup reduction),
-// t_i, v_i = fbar w_i psi'(r_i); colpart[g, :] = sum over the rows of
-// workgroup g of v_i A_i.  partials[g] = sum of t over its rows.
-// Returns hipErrorInvalidValue if cols exceed the register-resident limit.
-int64_t dense_fused_max_cols();
-hipError_t launch_dense_fused(const DenseView& d, const void* x, const double* fbar, int want_grad,
-                              double* partials, double* colpart, int ngroups, hipStream_t s);
-// grad[j] (=|+=) sum_g colpart[g, j] in fixed order (dtype of grad).
-hipError_t launch_dense_colsum(const double* colpart, int ngroups, int64_t cols, void* grad,
-                               Dtype dt, int accumulate, hipStream_t s);
-// Two-pass fallback: r = A x per row (one workgroup per row), v stored.
-hipError_t launch_dense_rows(const DenseView& d, const void* x, const double* fbar,
-                             double* partials, double* v, hipStream_t s);
-// grad (=|+=) A^T v (column-parallel).
-hipError_t launch_dense_cols(const DenseView& d, const double* v, void* grad, int accumulate,
-                             hipStream_t s);
+// How a dense objective runs: in one pass over A by teams of nw waves, or
+// (rows too long for their registers) in a row pass and a column pass.
+struct DenseCfg {
+    bool fused = false;
+    int nw = 1;          // waves of a team of the fused pass
+    int lanes = 64;      // lanes to a row; below 64, several rows share a wave
+    int bands = 1;       // row bands of the fused or the column pass (colpart rows)
+    int row_groups = 1;  // workgroups of the row pass
+};
+DenseCfg dense_config(const DenseView& d);
+// The single pass: per row r_i = A_i . x, t_i, v_i = fbar w_i psi'(r_i);
+// colpart[g, :] = sum over the rows of band g of v_i A_i (want_grad),
+// partials[g] = sum of t over its rows.  Without want_grad only one-wave
+// teams are offered (c.nw == 1).
+hipError_t launch_dense_fused(const DenseView& d, const DenseCfg& c, const void* x,
+                              const double* fbar, int want_grad, double* partials,
+                              double* colpart, hipStream_t s);
+// grad[j] (=|+=) sum_g colpart[g, j] in fixed order (dtype of grad); when
+// f_out is not null, also the sum of partials[0 .. np).
+hipError_t launch_dense_colsum(const double* colpart, int nbands, int64_t cols, void* grad,
+                               Dtype dt, int accumulate, const double* partials, int64_t np,
+                               double* f_out, hipStream_t s);
+// Row pass: r = A x, f's shares in partials[0 .. c.row_groups), v stored when not null.
+hipError_t launch_dense_rows(const DenseView& d, const DenseCfg& c, const void* x,
+                             const double* fbar, double* partials, double* v, hipStream_t s);
+// Column pass: colpart[g, :] = sum over the rows of band g of v_i A_i.
+hipError_t launch_dense_cols(const DenseView& d, const DenseCfg& c, const double* v,
+                             double* colpart, hipStream_t s);
 
 // --------------------------------------------------------- batched dense
 
