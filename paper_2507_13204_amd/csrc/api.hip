@@ -420,7 +420,8 @@ void layout_dense(pg_plan_s* p) {
 
 void layout_bdense(pg_plan_s* p) {
     Layout L;
-    p->bd_tiles = bdense_fwd_tiles(p->bd.m, p->bd.n);
+    p->bd.shape = bdense_shape(p->bd);
+    p->bd_tiles = bdense_fwd_tiles(p->bd);
     p->n_partials = (size_t)std::max<int64_t>(p->bd_tiles, 1);
     p->o_partials = L.take(sizeof(double) * p->n_partials);
     p->o_flag = L.take(sizeof(int32_t) * 4);

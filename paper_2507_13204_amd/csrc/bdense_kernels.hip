@@ -2,18 +2,17 @@
 //   forward   Y = A X,  f = sum W (.) psi(Y)  (epilogue),  V = W (.) psi'(Y)
 //   backward  G = fbar * A^T V
 //
-// Both products are m x m by m x n contractions, tiled 128 x 128 x 16 per
-// workgroup of 16 (FP64) or 8 (FP32) waves; each wave owns a 64 x 16 or
-// 64 x 32 block of C as MFMA 16x16x4 accumulators (FP64: v_mfma_f64_16x16x4_f64; FP32:
-// v_mfma_f32_16x16x4_f32, whose accumulation inside the instruction is FP32, so
-// the FP32 path adds each 16-deep k-tile's result into FP64 accumulators and
-// restarts the matrix-core accumulators from zero: FP32 sums stay 16 terms
-// long, every longer accumulation is FP64).
-// Tiles are staged k-major in LDS (double buffered, the next tile prefetched
-// into registers while the current one feeds the matrix cores).  The
-// nonlinearity and its derivative are fused into the forward epilogue, so
-// neither Y nor psi(Y) round-trips through HBM; the objective is reduced per
-// tile and then in a fixed order (deterministic).
+// Both products are m x m by m x n contractions on the matrix cores.  FP64:
+// v_mfma_f64_16x16x4_f64.  FP32: each operand is split into three bfloat16
+// parts (8 + 8 + 8 bits, nearest) and the six products that reach FP32
+// precision run on v_mfma_f32_16x16x32_bf16, smallest first; every 32 terms
+// the FP32 result is added into FP64 accumulators and the matrix-core
+// accumulators restart from zero, so every longer accumulation is FP64.  A wave
+// loads its operand fragments from global memory straight into the registers
+// the instruction reads, a k-step or more ahead, so there is no LDS staging
+// and no barrier in the k loop; the nonlinearity and its derivative are fused
+// into the forward epilogue, so neither Y nor psi(Y) round-trips through HBM;
+// the objective is reduced per tile and then in a fixed order (deterministic).
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -23,35 +22,19 @@ namespace pg {
 
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 16;
-// Workgroup shape per element type: the waves tile the 128 x 128 block as
-// 2 x WAVES_N blocks of 64 x WN, each wave holding 4 x NY MFMA accumulators.
-// One workgroup per compute unit at the benchmark's shape (256 tiles), so
-// more waves per workgroup is what hides the load and LDS latency: FP64
-// uses 16 waves (measured 0.70 -> 0.56 ms from 4 waves), FP32 8 (its
-// 16-byte loads need at least four elements per thread and operand).
-template <typename T>
-struct Cfg {
-    static constexpr int NTHR = sizeof(T) == 8 ? 1024 : 512;
-    static constexpr int WAVES_N = NTHR / 128, WN = BN / WAVES_N, NY = WN / 16;
-    static constexpr int kPerThread = BM * BK / NTHR;  // elements of each operand tile per thread
-};
-constexpr int PAD = 4;  // LDS row padding (elements) against bank conflicts on transposed stores
-
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
+// E: consecutive k a lane holds of a k-step of 4 E (lane group lk = lane / 16
+// holds k = E lk + e).
 template <typename T>
 struct Mfma;
 
 template <>
 struct Mfma<double> {
     using acc_t = d4;
-    __device__ static acc_t zero() { return acc_t{0.0, 0.0, 0.0, 0.0}; }
-    __device__ static acc_t mac(double a, double b, acc_t c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    __device__ static double get(const acc_t& c, int r) { return c[r]; }
+    static constexpr int E = 4;
     // Output row (within the 16 x 16 block) of register r in lanes 16*g .. 16*g+15.
     __device__ static int row(int g, int r) { return g + 4 * r; }
 };
@@ -59,259 +42,443 @@ struct Mfma<double> {
 template <>
 struct Mfma<float> {
     using acc_t = f4;
-    __device__ static acc_t zero() { return acc_t{0.f, 0.f, 0.f, 0.f}; }
-    __device__ static acc_t mac(float a, float b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static double get(const acc_t& c, int r) { return (double)c[r]; }
+    static constexpr int E = 8;
     __device__ static int row(int g, int r) { return 4 * g + r; }
 };
 
+// 2^16 v = h + m + l, each the nearest bfloat16 of what is left: bfloat16 has
+// FP32's exponents but ends at 2^-133, 16 places above FP32's last subnormal
+// bit, so the factor keeps the low parts of the smallest values.  A value that
+// the factor takes past the largest bfloat16, an infinity or a NaN has parts
+// that are not finite, and so have the products (the caller then repeats
+// them in FP32).
+constexpr float kSplitScale = 65536.f;
+struct Split {
+    uint32_t h[4], m[4], l[4];  // two parts to a register
+};
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2));
+}
+__device__ __forceinline__ float low_bf16(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float high_bf16(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+__device__ __forceinline__ bf8 parts(const uint32_t (&p)[4]) { return __builtin_bit_cast(bf8, p); }
+
+__device__ __forceinline__ Split split3(const float (&v)[8]) {
+    Split s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float v0 = v[2 * e] * kSplitScale, v1 = v[2 * e + 1] * kSplitScale;
+        s.h[e] = pack_bf16(v0, v1);
+        const float r0 = v0 - low_bf16(s.h[e]), r1 = v1 - high_bf16(s.h[e]);
+        s.m[e] = pack_bf16(r0, r1);
+        s.l[e] = pack_bf16(r0 - low_bf16(s.m[e]), r1 - high_bf16(s.m[e]));
+    }
+    return s;
+}
+
+// 32 products per entry.  What is left out (m l, l m, l l) is below 2^-24 of
+// a product.  Against FP64 on a ~ N(0,1/m), b ~ U(-1,1): 3.7e-8 (2-norm) per
+// 32 terms, against 7.4e-8 for two 16-term chains of v_mfma_f32_16x16x4_f32.
+__device__ __forceinline__ f4 mma_split(const Split& a, const Split& b) {
+    const bf8 ah = parts(a.h), am = parts(a.m), al = parts(a.l);
+    const bf8 bh = parts(b.h), bm = parts(b.m), bl = parts(b.l);
+    f4 c = {0.f, 0.f, 0.f, 0.f};
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, bm, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, bh, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bm, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, c, 0, 0, 0);
+    return c;
+}
 
 enum Epi { EPI_FWD = 0, EPI_BWD = 1 };
 
-// One k-tile of both operands staged in registers on its way to LDS.
+// VN consecutive elements with the alignment of one (the compiler picks the
+// widest load the target allows for it).
+template <typename T, int VN>
+__device__ __forceinline__ void load_vec(const T* __restrict__ p, T (&o)[VN]) {
+    typedef T V __attribute__((ext_vector_type(VN), aligned(sizeof(T))));
+    const V v = *reinterpret_cast<const V*>(p);
+#pragma unroll
+    for (int c = 0; c < VN; ++c) o[c] = v[c];
+}
 template <typename T>
-struct Stage {
-    T a[Cfg<T>::kPerThread];
-    T b[Cfg<T>::kPerThread];
+__device__ __forceinline__ void load_vec(const T* __restrict__ p, T (&o)[1]) {
+    o[0] = *p;
+}
+
+// Tile shape: a wave owns BX x BY MFMA blocks (16 BX x 16 BY of C); a
+// workgroup has WM x WN such wave tiles and KW waves on each, which split the
+// contraction among them and are summed through LDS.  D k-steps are in
+// flight; the registers allow OCC waves per SIMD at least.
+template <int BX_, int BY_, int WM_, int WN_, int KW_, int D64, int D32, int OCC_>
+struct Shape {
+    static constexpr int BX = BX_, BY = BY_, WM = WM_, WN = WN_, KW = KW_, OCC = OCC_;
+    template <typename T>
+    static constexpr int D = sizeof(T) == 8 ? D64 : D32;
+    static constexpr int NWAVES = WM * WN * KW, NTHR = 64 * NWAVES;
+    static constexpr int TM = 16 * BX * WM, TN = 16 * BY * WN;
+};
+
+// One k-step of both operands as a lane holds them.
+template <typename T, int BX, int BY>
+struct Frag {
+    T a[Mfma<T>::E][BX];
+    T b[Mfma<T>::E][BY];
 };
 
 // C[M x N] = op(A)[M x K] * Bm[K x N].
-//   TRANS_A == false: op(A)[i][k] = A[i * lda + k]   (forward, A is m x m)
-//   TRANS_A == true:  op(A)[i][k] = A[k * lda + i]   (backward, A^T)
-// FULL: every tile is in bounds and rows are 16-byte aligned, so operands are
-// read with 16-byte vector loads and no bounds checks.  The k loop keeps two
-// tiles in flight in registers (loaded two steps ahead) on top of the LDS
-// double buffer: at one workgroup per compute unit the matrix-core time of a
-// k-step is shorter than the latency of its loads.
-template <typename T, bool TRANS_A, int EPI, bool FULL>
-__global__ void __launch_bounds__(Cfg<T>::NTHR)
+//   TRANS_A == false: op(A)[i][k] = A[i * K + k]   (forward, A is m x m)
+//   TRANS_A == true:  op(A)[i][k] = A[k * M + i]   (backward, A^T)
+// A lane's rows of a block are i0 + 16 x + li (forward; consecutive k in one
+// load) or i0 + BX li + x (backward; BX consecutive rows in one load); its
+// columns are j0 + BY li + y, so operand B, C and W are read and written BY
+// columns at a time.  A wave whose block would reach past the edge takes the
+// last whole block instead and stores only its own part of it (a block of one
+// 16 x 16 reads the last row or column again instead), so the loads need no
+// bounds checks; the caller offers only shapes whose blocks fit C.
+//
+// Bound by the matrix cores in FP64 (66 TFLOP/s of 78.6 at 4096 x 1024, 59 with
+// the tiles staged through LDS and a barrier per k-step), by the vector
+// instructions of the split and the FP64 sums in FP32 (118 TFLOP/s, 100 on
+// v_mfma_f32_16x16x4_f32 through LDS), and by latency below some 500 x 500:
+// 257 x 129 takes 13 us per gradient (106 / 81 before, in 128 x 128 tiles).
+template <typename T, bool TRANS_A, int EPI, typename S>
+__global__ void __launch_bounds__(S::NTHR, S::OCC)
 k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_t N, int64_t K,
             const T* __restrict__ W, double* __restrict__ partials, T* __restrict__ Vout,
-            const double* __restrict__ fbar, T* __restrict__ Gout, int accumulate) {
+            const double* __restrict__ fbar, T* __restrict__ Gout, int accumulate, int tiles_n) {
     using MF = Mfma<T>;
     using acc_t = typename MF::acc_t;
-    constexpr int NTHR = Cfg<T>::NTHR, WAVES_N = Cfg<T>::WAVES_N, WN = Cfg<T>::WN, NY = Cfg<T>::NY;
-    constexpr int kPerThread = Cfg<T>::kPerThread;
-    // Vector width of the operand loads: 16 bytes, or fewer elements when a
-    // thread moves fewer per tile.
-    constexpr int VN = (int)(16 / sizeof(T)) < kPerThread ? (int)(16 / sizeof(T)) : kPerThread;
-    constexpr int NV = kPerThread / VN;  // vectors per operand per thread
-    static_assert(NV >= 1 && kPerThread % VN == 0, "16-byte loads need whole vectors per thread");
-    static_assert(NY >= 1 && WN % 16 == 0, "each wave needs whole 16-column MFMA blocks");
-    __shared__ T As[2][BK][BM + PAD];
-    __shared__ T Bs[2][BK][BN + PAD];
-    __shared__ double red[NTHR / kWave];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wid = tid >> 6;
-    const int wm = wid / WAVES_N, wn = wid % WAVES_N;  // wave's 64 x WN block within the tile
-    const int64_t i0 = (int64_t)blockIdx.y * BM, j0 = (int64_t)blockIdx.x * BN;
-
-    // Element q of this thread's share of a tile, as (i, k) of op(A) and (k, j) of B.
-    auto a_coord = [&](int q, int& ii, int& kk) {
-        if constexpr (FULL) {
-            const int v = tid + NTHR * (q / VN), c = q % VN;
-            if (TRANS_A) {
-                kk = v / (BM / VN);
-                ii = (v % (BM / VN)) * VN + c;
-            } else {
-                ii = v / (BK / VN);
-                kk = (v % (BK / VN)) * VN + c;
-            }
-        } else {
-            const int p = tid + NTHR * q;
-            if (TRANS_A) {
-                kk = p / BM;
-                ii = p % BM;
-            } else {
-                ii = p / BK;
-                kk = p % BK;
-            }
-        }
-    };
-    auto b_coord = [&](int q, int& kk, int& jj) {
-        if constexpr (FULL) {
-            const int v = tid + NTHR * (q / VN), c = q % VN;
-            kk = v / (BN / VN);
-            jj = (v % (BN / VN)) * VN + c;
-        } else {
-            const int p = tid + NTHR * q;
-            kk = p / BN;
-            jj = p % BN;
-        }
-    };
-    auto gload = [&](Stage<T>& st, int64_t k0) {
-        if constexpr (FULL) {
-            typedef T V __attribute__((ext_vector_type(VN)));
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                int ii, kk, bk, bj;
-                a_coord(v * VN, ii, kk);
-                b_coord(v * VN, bk, bj);
-                const T* pa = TRANS_A ? A + (k0 + kk) * K + (i0 + ii) : A + (i0 + ii) * K + (k0 + kk);
-                const V va = *reinterpret_cast<const V*>(pa);
-                const V vb = *reinterpret_cast<const V*>(Bm + (k0 + bk) * N + (j0 + bj));
-#pragma unroll
-                for (int c = 0; c < VN; ++c) {
-                    st.a[v * VN + c] = va[c];
-                    st.b[v * VN + c] = vb[c];
-                }
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < kPerThread; ++q) {
-                int ii, kk, bk, bj;
-                a_coord(q, ii, kk);
-                b_coord(q, bk, bj);
-                const int64_t gi = i0 + ii, gk = k0 + kk;
-                T va = T(0);
-                if (gi < M && gk < K) va = TRANS_A ? A[gk * K + gi] : A[gi * K + gk];
-                st.a[q] = va;
-                const int64_t gk2 = k0 + bk, gj = j0 + bj;
-                st.b[q] = (gk2 < K && gj < N) ? Bm[gk2 * N + gj] : T(0);
-            }
-        }
-    };
-    auto lstore = [&](const Stage<T>& st, int buf) {
-#pragma unroll
-        for (int q = 0; q < kPerThread; ++q) {
-            int ii, kk, bk, bj;
-            a_coord(q, ii, kk);
-            b_coord(q, bk, bj);
-            As[buf][kk][ii] = st.a[q];
-            Bs[buf][bk][bj] = st.b[q];
-        }
-    };
-
-    acc_t acc[4][NY];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < NY; ++b) acc[a][b] = MF::zero();
-    // FP32 operands: FP64 running sums of the per-k-tile MFMA results.
+    constexpr int BX = S::BX, BY = S::BY, D = S::template D<T>, KW = S::KW;
+    constexpr int E = MF::E, KS = 4 * E;  // k per lane and per step
     constexpr bool kWide = std::is_same<T, float>::value;
-    double wide[kWide ? 4 : 1][kWide ? NY : 1][4];
-    if constexpr (kWide) {
+    using F = Frag<T, BX, BY>;
+    __shared__ double red[S::NWAVES];
+
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int wmn = wid % (S::WM * S::WN), kw = wid / (S::WM * S::WN);
+    const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
+    // First row / column of wave block q, and of the whole block it reads.
+    const int64_t ti = (int64_t)(tile / tiles_n) * S::TM, tj = (int64_t)(tile % tiles_n) * S::TN;
+    auto own_i = [&](int q) { return ti + (q / S::WN) * (16 * BX); };
+    auto own_j = [&](int q) { return tj + (q % S::WN) * (16 * BY); };
+    auto low = [](int64_t a, int64_t b) { return a < b ? a : b; };
+    auto read_i = [&](int64_t i) { return BX > 1 ? low(i, M - 16 * BX) : i; };
+    auto read_j = [&](int64_t j) { return BY > 1 ? low(j, N - 16 * BY) : j; };
+    const int64_t i0 = read_i(own_i(wmn)), j0 = read_j(own_j(wmn));
+    const bool any = own_i(wmn) < M && own_j(wmn) < N;
+
+    // This wave's k range: whole steps, the remainder of K with the last one.
+    const int64_t steps = K / KS;
+    const int64_t t0 = steps * kw / KW, t1 = steps * (kw + 1) / KW;
+    const int64_t kbeg = t0 * KS, kend = kw == KW - 1 ? K : t1 * KS;
+
+    const T* pa[TRANS_A ? 1 : BX];
+    if constexpr (TRANS_A) {
+        pa[0] = A + low(i0 + BX * li, M - BX) + (kbeg + E * lk) * M;
+    } else {
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < NY; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) wide[a][b][r] = 0.0;
+        for (int x = 0; x < BX; ++x) pa[x] = A + low(i0 + 16 * x + li, M - 1) * K + (kbeg + E * lk);
     }
-    auto fold = [&]() {
-        if constexpr (kWide) {
+    const T* pb = Bm + low(j0 + BY * li, N - BY) + (kbeg + E * lk) * N;
+
+    // FP64: the running sums; FP32: unused but by the repeat in FP32
+    acc_t acc[BX][BY];
+    double wide[kWide ? BX : 1][kWide ? BY : 1][4];
+    auto clear = [&]() {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+        for (int x = 0; x < BX; ++x)
 #pragma unroll
-                for (int b = 0; b < NY; ++b) {
+            for (int y = 0; y < BY; ++y) {
+                acc[x][y] = acc_t{0, 0, 0, 0};
+                if constexpr (kWide)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) wide[a][b][r] += MF::get(acc[a][b], r);
-                    acc[a][b] = MF::zero();
+                    for (int r = 0; r < 4; ++r) wide[x][y][r] = 0.0;
+            }
+    };
+    clear();
+    auto load = [&](F& f, int64_t t) {
+        const int64_t k = t * KS;
+        if constexpr (!TRANS_A) {
+#pragma unroll
+            for (int x = 0; x < BX; ++x) {
+                T v[E];
+                load_vec<T, E>(pa[x] + k, v);
+#pragma unroll
+                for (int e = 0; e < E; ++e) f.a[e][x] = v[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) load_vec(pa[0] + (k + e) * M, f.a[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) load_vec(pb + (k + e) * N, f.b[e]);
+    };
+    // The products of one k-step; next() is called once f has been read.
+    auto mma = [&](const F& f, auto next) {
+        if constexpr (!kWide) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+#pragma unroll
+                    for (int y = 0; y < BY; ++y)
+                        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[s][x], f.b[s][y], acc[x][y], 0, 0, 0);
+            next();
+        } else {
+            Split a[BX], b[BY];
+#pragma unroll
+            for (int x = 0; x < BX; ++x) {
+                float v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = f.a[e][x];
+                a[x] = split3(v);
+            }
+#pragma unroll
+            for (int y = 0; y < BY; ++y) {
+                float v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = f.b[e][y];
+                b[y] = split3(v);
+            }
+            next();
+#pragma unroll
+            for (int y = 0; y < BY; ++y)
+#pragma unroll
+                for (int x = 0; x < BX; ++x) {
+                    const f4 c = mma_split(a[x], b[y]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)c[r];
                 }
         }
     };
-
-    const int li = lane & 15, lk = lane >> 4;
-    auto compute = [&](int buf) {
+    if (any) {
+        F f[D];
+        const int64_t n = t1 - t0;
 #pragma unroll
-        for (int ks = 0; ks < BK / 4; ++ks) {
-            T a[4], b[NY];
+        for (int d = 0; d < D; ++d)
+            if (d < n) load(f[d], d);
+        int64_t t = 0;
+        for (; t + 2 * D <= n; t += D) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) a[x] = As[buf][ks * 4 + lk][wm * 64 + x * 16 + li];
-#pragma unroll
-            for (int y = 0; y < NY; ++y) b[y] = Bs[buf][ks * 4 + lk][wn * WN + y * 16 + li];
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < NY; ++y) acc[x][y] = MF::mac(a[x], b[y], acc[x][y]);
+            for (int d = 0; d < D; ++d) mma(f[d], [&] { load(f[d], t + d + D); });
         }
-    };
-
-    // Tile j lives in stage j % 2 and LDS buffer j % 2.
-    const int64_t nk = (K + BK - 1) / BK;
-    Stage<T> s0, s1;
-    if (nk > 0) gload(s0, 0);
-    if (nk > 1) gload(s1, BK);
-    if (nk > 0) lstore(s0, 0);
-    __syncthreads();
-    for (int64_t t = 0; t < nk; t += 2) {
-        // even step: compute tile t from buffer 0; tile t+1 waits in s1
-        if (t + 2 < nk) gload(s0, (t + 2) * BK);
-        compute(0);
-        fold();
-        if (t + 1 < nk) lstore(s1, 1);
-        __syncthreads();
-        if (t + 1 >= nk) break;
-        // odd step: compute tile t+1 from buffer 1; tile t+2 waits in s0
-        if (t + 3 < nk) gload(s1, (t + 3) * BK);
-        compute(1);
-        fold();
-        if (t + 2 < nk) lstore(s0, 0);
-        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (t + d < n)
+                mma(f[d], [&] {
+                    if (t + d + D < n) load(f[d], t + d + D);
+                });
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (t + d + D < n) mma(f[d], [] {});
+        if (t1 * KS < kend) {
+            // the last K % KS products: k past the end contributes zero
+            const int64_t k0 = n * KS;
+            F z;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const bool in = t1 * KS + E * lk + e < K;
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+                    z.a[e][x] = in ? (TRANS_A ? pa[0][(k0 + e) * M + x] : pa[TRANS_A ? 0 : x][k0 + e]) : T(0);
+#pragma unroll
+                for (int y = 0; y < BY; ++y) z.b[e][y] = in ? pb[(k0 + e) * N + y] : T(0);
+            }
+            mma(z, [] {});
+        }
+        if constexpr (kWide) {
+            // An operand or a sum that is not finite: the whole block again on
+            // the FP32 instruction, whose infinities are those of the sums.
+            bool bad = false;
+#pragma unroll
+            for (int x = 0; x < BX; ++x)
+#pragma unroll
+                for (int y = 0; y < BY; ++y)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        wide[x][y][r] *= 1.0 / ((double)kSplitScale * kSplitScale);
+                        bad |= !__builtin_isfinite(wide[x][y][r]);
+                    }
+            if (__any(bad)) {
+                clear();
+                const int64_t ra = kbeg + E * lk, rb = ra;  // k of pa[.][0] and pb[0]
+                for (int64_t k0 = kbeg; k0 < kend; k0 += 16) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        const int64_t k = k0 + 4 * s + lk;
+                        const bool in = k < kend;
+                        T av[BX], bv[BY];
+#pragma unroll
+                        for (int x = 0; x < BX; ++x)
+                            av[x] = in ? (TRANS_A ? pa[0][(k - ra) * M + x] : pa[TRANS_A ? 0 : x][k - ra]) : T(0);
+#pragma unroll
+                        for (int y = 0; y < BY; ++y) bv[y] = in ? pb[(k - rb) * N + y] : T(0);
+#pragma unroll
+                        for (int x = 0; x < BX; ++x)
+#pragma unroll
+                            for (int y = 0; y < BY; ++y)
+                                acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[x], bv[y], acc[x][y], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int x = 0; x < BX; ++x)
+#pragma unroll
+                        for (int y = 0; y < BY; ++y) {
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)acc[x][y][r];
+                            acc[x][y] = acc_t{0, 0, 0, 0};
+                        }
+                }
+            }
+        }
     }
 
-    // Accumulator (x, y) register r of lane l holds C[row][col] with
-    // col = y*16 + l%16 and row = x*16 + MF::row(l/16, r) inside the wave
-    // block: the FP64 instruction interleaves rows across registers
-    // (l/16 + 4r), the FP32 one keeps them in consecutive registers
-    // (4(l/16) + r).
     double tsum = 0.0;
     const double fb = (EPI == EPI_BWD && fbar) ? fbar[0] : 1.0;
+    // Stores an entry of wave block q unless it belongs to another wave.
+    auto emit = [&](int q, int64_t gi, int64_t gj, double c) {
+        if (gi < own_i(q) || gi >= M || gj < own_j(q) || gj >= N) return;
+        const int64_t o = gi * N + gj;
+        if constexpr (EPI == EPI_FWD) {
+            const double s2 = c * c, wv = to_f64(W[o]);
+            tsum += wv * psi_from_sq(s2);
+            if (Vout) Vout[o] = static_cast<T>(wv * dpsi_from(c, s2));
+        } else {
+            const double g = fb * c;
+            Gout[o] = accumulate ? static_cast<T>(to_f64(Gout[o]) + g) : static_cast<T>(g);
+        }
+    };
+    auto value = [&](int x, int y, int r) -> double {
+        if constexpr (kWide)
+            return wide[x][y][r];
+        else
+            return acc[x][y][r];
+    };
+    // Register r of lane (li, lk) holds row MF::row(lk, r) and column li of a
+    // block: the FP64 instruction interleaves rows across registers (lk + 4r),
+    // the FP32 one keeps them in consecutive registers (4 lk + r).
+    auto row_of = [&](int x, int rho) { return TRANS_A ? BX * rho + x : 16 * x + rho; };
+    if constexpr (KW == 1) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+        for (int x = 0; x < BX; ++x)
 #pragma unroll
-        for (int y = 0; y < NY; ++y)
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t gi = i0 + wm * 64 + x * 16 + MF::row(lk, r);
-                const int64_t gj = j0 + wn * WN + y * 16 + li;
-                if (gi < M && gj < N) {
-                    double c;
-                    if constexpr (kWide)
-                        c = wide[x][y][r];
-                    else
-                        c = MF::get(acc[x][y], r);
-                    const int64_t o = gi * N + gj;
-                    if constexpr (EPI == EPI_FWD) {
-                        const double s2 = c * c, wv = to_f64(W[o]);
-                        tsum += wv * psi_from_sq(s2);
-                        if (Vout) Vout[o] = static_cast<T>(wv * dpsi_from(c, s2));
-                    } else {
-                        const double g = fb * c;
-                        Gout[o] = accumulate ? static_cast<T>(to_f64(Gout[o]) + g) : static_cast<T>(g);
-                    }
-                }
-            }
-    if constexpr (EPI == EPI_FWD) {
-        const double s = block_sum<NTHR>(tsum, red);
-        if (tid == 0) partials[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+                for (int y = 0; y < BY; ++y)
+                    emit(wmn, i0 + row_of(x, MF::row(lk, r)), j0 + BY * li + y, value(x, y, r));
+    } else {
+        // The KW partial sums of each entry, added in ascending k order; the
+        // entries are dealt to all the waves.
+        constexpr int NS = S::WM * S::WN * BX * BY * 4;  // 64-entry slices of the tile
+        __shared__ double part[KW][NS][64];
+#pragma unroll
+        for (int x = 0; x < BX; ++x)
+#pragma unroll
+            for (int y = 0; y < BY; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[kw][((wmn * BX + x) * BY + y) * 4 + r][lane] = value(x, y, r);
+        __syncthreads();
+        for (int q = wid; q < NS; q += S::NWAVES) {
+            double c = part[0][q][lane];
+#pragma unroll
+            for (int k = 1; k < KW; ++k) c += part[k][q][lane];
+            const int r = q & 3, y = (q >> 2) % BY, x = (q >> 2) / BY % BX, w2 = (q >> 2) / (BX * BY);
+            emit(w2, read_i(own_i(w2)) + row_of(x, MF::row(lk, r)), read_j(own_j(w2)) + BY * li + y, c);
+        }
     }
+    if constexpr (EPI == EPI_FWD) {
+        const double s = block_sum<S::NTHR>(tsum, red);
+        if (threadIdx.x == 0) partials[tile] = s;
+    }
+}
+
+// A workgroup has eight waves in every shape; they share a tile by splitting
+// it or the contraction.  Large tiles move the fewest operand bytes, small
+// ones fill the device when C is small.  Two workgroups per compute unit (four
+// waves per SIMD) with one k-step in flight beat one with two or three for the
+// middle shapes (3,000 x 500, FP64 / FP32: 64 x 32 341 / 255 -> 334 / 230 us,
+// 32 x 32 381 / 308 -> 353 / 244 us).
+using S0 = Shape<4, 2, 2, 4, 1, 2, 1, 2>;  // 128 x 128
+using S1 = Shape<4, 2, 1, 4, 2, 2, 1, 2>;  // 64 x 128
+using S2 = Shape<2, 2, 2, 2, 2, 1, 1, 4>;  // 64 x 64
+using S3 = Shape<2, 2, 2, 1, 4, 1, 1, 4>;  // 64 x 32
+using S4 = Shape<2, 2, 1, 1, 8, 1, 1, 4>;  // 32 x 32
+using S5 = Shape<2, 1, 1, 1, 8, 3, 2, 2>;  // 32 x 16
+using S6 = Shape<1, 1, 1, 1, 8, 4, 2, 2>;  // 16 x 16, the one that takes any size
+struct ShapeInfo {
+    int tm, tn, bx, by;
+    double cost[2];  // FP64, FP32
+};
+template <typename S>
+constexpr ShapeInfo info(double c64, double c32) {
+    return {S::TM, S::TN, S::BX, S::BY, {c64, c32}};
+}
+// cost: picoseconds per product and entry of a tile with every compute unit
+// busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.
+constexpr ShapeInfo kShapes[] = {info<S0>(7.7, 4.3), info<S1>(7.8, 4.5),  info<S2>(9.1, 5.5),
+                                 info<S3>(9.1, 6.2), info<S4>(10.0, 6.6), info<S5>(16.0, 8.9),
+                                 info<S6>(22.7, 11.4)};
+constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
+
+int64_t tiles_of(const BDenseView& b, int sh) {
+    const ShapeInfo& s = kShapes[sh];
+    return ((b.m + s.tm - 1) / s.tm) * ((b.n + s.tn - 1) / s.tn);
 }
 
 }  // namespace
 
-int64_t bdense_fwd_tiles(int64_t m, int64_t n) { return ((m + BM - 1) / BM) * ((n + BN - 1) / BN); }
+// The shape with the least time for its rounds of 256 tiles, one to a compute
+// unit.  Measured gradients that the rule decides (FP64 / FP32, us): 3,000 x
+// 500: 725 / 403 in 128 x 128 tiles (96 of them), 373 / 218 in 64 x 128 (188),
+// 334 / 230 in 64 x 32 (752); 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
+// 32 x 16; 4,096 x 1,024: 1,043 / 588 in 128 x 128, 1,189 / 730 in 64 x 64.
+int bdense_shape(const BDenseView& b) {
+    int best = kNShapes - 1;
+    double tbest = 1e300;
+    for (int i = 0; i < kNShapes; ++i) {
+        const ShapeInfo& s = kShapes[i];
+        if ((s.bx > 1 && b.m < 16 * s.bx) || (s.by > 1 && b.n < 16 * s.by)) continue;
+        const double t = (double)((tiles_of(b, i) + 255) / 256) * s.tm * s.tn * s.cost[b.dtype == F64 ? 0 : 1];
+        if (t < tbest) {
+            tbest = t;
+            best = i;
+        }
+    }
+    return best;
+}
+
+int64_t bdense_fwd_tiles(const BDenseView& b) { return tiles_of(b, b.shape); }
 
 namespace {
 
-// Vector path: whole tiles only, and the per-call operand (X or V) 16-byte
-// aligned (A and W are checked when the plan is made).
-bool full_tiles(const BDenseView& b, const void* op) {
-    return b.m % BM == 0 && b.n % BN == 0 && b.m % BK == 0 && (uintptr_t)op % 16 == 0;
+template <typename T, bool TRANS, int EPI, typename S>
+hipError_t launch_shape(const BDenseView& b, hipStream_t s, const T* A, const T* Bm, const T* W,
+                        double* partials, T* V, const double* fbar, T* G, int accumulate) {
+    const int64_t tn = (b.n + S::TN - 1) / S::TN, nt = tn * ((b.m + S::TM - 1) / S::TM);
+    if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
+    PG_LAUNCH((k_gemm_mfma<T, TRANS, EPI, S>), dim3((unsigned)nt), dim3(S::NTHR), 0, s, A, Bm, b.m,
+              b.n, b.m, W, partials, V, fbar, G, accumulate, (int)tn);
+    return hipGetLastError();
 }
 
 template <typename T, bool TRANS, int EPI>
-void launch_gemm(const BDenseView& b, dim3 grid, hipStream_t s, const T* A, const T* Bm, const T* W,
-                 double* partials, T* V, const double* fbar, T* G, int accumulate) {
-    if (full_tiles(b, Bm))
-        PG_LAUNCH((k_gemm_mfma<T, TRANS, EPI, true>), grid, dim3(Cfg<T>::NTHR), 0, s, A, Bm, b.m,
-                           b.n, b.m, W, partials, V, fbar, G, accumulate);
-    else
-        PG_LAUNCH((k_gemm_mfma<T, TRANS, EPI, false>), grid, dim3(Cfg<T>::NTHR), 0, s, A, Bm, b.m,
-                           b.n, b.m, W, partials, V, fbar, G, accumulate);
+hipError_t launch_gemm(const BDenseView& b, hipStream_t s, const T* A, const T* Bm, const T* W,
+                       double* partials, T* V, const double* fbar, T* G, int accumulate) {
+    switch (b.shape) {
+        case 0: return launch_shape<T, TRANS, EPI, S0>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 1: return launch_shape<T, TRANS, EPI, S1>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 2: return launch_shape<T, TRANS, EPI, S2>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 3: return launch_shape<T, TRANS, EPI, S3>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 4: return launch_shape<T, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 5: return launch_shape<T, TRANS, EPI, S5>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 6: return launch_shape<T, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -319,29 +486,23 @@ void launch_gemm(const BDenseView& b, dim3 grid, hipStream_t s, const T* A, cons
 hipError_t launch_bdense_fwd(const BDenseView& b, const void* X, double* partials, void* V,
                              hipStream_t s) {
     if (b.m == 0 || b.n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((b.n + BN - 1) / BN), (unsigned)((b.m + BM - 1) / BM));
     if (b.dtype == F64)
-        launch_gemm<double, false, EPI_FWD>(b, grid, s, (const double*)b.A, (const double*)X,
-                                            (const double*)b.W, partials, (double*)V, nullptr,
-                                            nullptr, 0);
-    else
-        launch_gemm<float, false, EPI_FWD>(b, grid, s, (const float*)b.A, (const float*)X,
-                                           (const float*)b.W, partials, (float*)V, nullptr,
-                                           nullptr, 0);
-    return hipGetLastError();
+        return launch_gemm<double, false, EPI_FWD>(b, s, (const double*)b.A, (const double*)X,
+                                                   (const double*)b.W, partials, (double*)V, nullptr,
+                                                   nullptr, 0);
+    return launch_gemm<float, false, EPI_FWD>(b, s, (const float*)b.A, (const float*)X,
+                                              (const float*)b.W, partials, (float*)V, nullptr,
+                                              nullptr, 0);
 }
 
 hipError_t launch_bdense_bwd(const BDenseView& b, const void* V, const double* fbar, void* G,
                              int accumulate, hipStream_t s) {
     if (b.m == 0 || b.n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((b.n + BN - 1) / BN), (unsigned)((b.m + BM - 1) / BM));
     if (b.dtype == F64)
-        launch_gemm<double, true, EPI_BWD>(b, grid, s, (const double*)b.A, (const double*)V, nullptr,
-                                           nullptr, nullptr, fbar, (double*)G, accumulate);
-    else
-        launch_gemm<float, true, EPI_BWD>(b, grid, s, (const float*)b.A, (const float*)V, nullptr,
-                                          nullptr, nullptr, fbar, (float*)G, accumulate);
-    return hipGetLastError();
+        return launch_gemm<double, true, EPI_BWD>(b, s, (const double*)b.A, (const double*)V, nullptr,
+                                                  nullptr, nullptr, fbar, (double*)G, accumulate);
+    return launch_gemm<float, true, EPI_BWD>(b, s, (const float*)b.A, (const float*)V, nullptr,
+                                             nullptr, nullptr, fbar, (float*)G, accumulate);
 }
 
 }  // namespace pg

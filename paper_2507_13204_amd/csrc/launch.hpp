@@ -309,12 +309,16 @@ struct BDenseView {
     Dtype dtype = F64;
     const void* A = nullptr;
     const void* W = nullptr;
+    int shape = 0;  // tile shape (bdense_shape)
 };
+
+// Tile shape of the products for these sizes.
+int bdense_shape(const BDenseView& b);
 
 // Forward: Y = A X on the matrix cores with the epilogue
 // t = W psi(Y) (per-tile partial sums) and, when V != nullptr,
 // V = W psi'(Y) (FP64 or dtype per vdt).
-int64_t bdense_fwd_tiles(int64_t m, int64_t n);
+int64_t bdense_fwd_tiles(const BDenseView& b);
 hipError_t launch_bdense_fwd(const BDenseView& b, const void* X, double* partials, void* V,
                              hipStream_t s);
 // Backward: G (=|+=) fbar * A^T V.
