@@ -442,7 +442,12 @@ pg_status pg_prog_plan(pg_prog prog, size_t* workspace_bytes);
 /* workspace: device memory of at least the planned bytes, 256-byte aligned,
  * owned by the caller and used by every later run (tape, shadows, partials).
  * Checks every gather's connectivity against its operand on the device, on the
- * null stream, and waits for it (PG_ERANGE if an entry is out of range). */
+ * null stream, and waits for it (PG_ERANGE if an entry is out of range).  For
+ * gathers of 2^16 to 2^23 incidences whose sampled rows share few cache lines
+ * it also lists where each incidence falls in the transposed connectivity, so
+ * that the reverse is stores and a sum per entry instead of atomics; runs
+ * compare conn with what the list was built from, and go back to atomics for
+ * good (until bound again) once it differs. */
 pg_status pg_prog_bind_workspace(pg_prog prog, void* workspace, size_t bytes);
 /* inputs: host array of device pointers, one per input in creation order.
  * f_out: device FP64 (may be NULL).  grads: NULL (objective only) or a host
@@ -458,7 +463,8 @@ typedef struct {
     int32_t fwd_kernels;      /* launches of the forward pass (shadow clearing not counted) */
     int32_t rev_kernels;      /* launches of the reverse pass */
     int32_t atomic_ops;       /* reverse deliveries made atomic by the race rule (gathers) */
-    int32_t rescheduled_ops;  /* reverse stencils rescheduled into gathers (no atomics) */
+    int32_t rescheduled_ops;  /* reverse stencils rescheduled into gathers (no atomics), and,
+                                 once bound, gathers delivered in transposed order */
     int32_t groups;           /* fused groups of pointwise constructs (the sum's included) */
     int32_t fused_gathers;    /* gathers evaluated inside their consuming group */
     int32_t dead_ops;         /* constructs that do not feed the sum (never run) */

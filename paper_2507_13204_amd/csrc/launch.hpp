@@ -209,11 +209,15 @@ hipError_t launch_validate_count(const int32_t* conn, int64_t n_items, int64_t n
 // workgroup of the pass probes.
 hipError_t launch_table_check(const int32_t* conn, int64_t n_elems, int32_t k, int64_t span,
                               uint32_t shift, int slots, int32_t* miss, hipStream_t s);
+// *out = max(*out, v[0..n)).
+hipError_t launch_max(const int32_t* v, int64_t n, int32_t* out, hipStream_t s);
 // Exclusive scan: out[0..n] with out[n] = total.  scratch holds
 // scan_scratch_items(n) int64 values.
 int64_t scan_scratch_items(int64_t n);
 hipError_t launch_exclusive_scan(const int32_t* in, int64_t n, int32_t* out, int64_t* scratch,
                                  hipStream_t s);
+// pos[inc[q]] = q for q < n.
+hipError_t launch_invert(const int32_t* inc, int64_t n, int32_t* pos, hipStream_t s);
 // inc[cursor[conn[i]]++] = i, then each row of inc sorted ascending.
 hipError_t launch_csr_fill_sort(const int32_t* conn, int64_t n_items, int64_t n_nodes,
                                 const int32_t* offs, int32_t* cursor, int32_t* inc, hipStream_t s);
@@ -417,6 +421,16 @@ struct GroupDev {
     const double* gB = nullptr;
     const double* gsrc = nullptr;
     double* gsrc_shadow = nullptr;
+    // Reverse of the gather through its transposed connectivity: the products
+    // B adj are written to gather_prod at gather_pos (their places in it)
+    // instead of scattered, the adjoint to gather_adj, and the rows are
+    // compared with those the places were computed from (*stale is set to 1
+    // where they differ).
+    double* gather_adj = nullptr;
+    double* gather_prod = nullptr;
+    const int32_t* gather_pos = nullptr;
+    const int32_t* conn_copy = nullptr;
+    int32_t* stale = nullptr;
     uint32_t hash_shift = kHashRotDefault;
     int agg_slots = 4096;  // LDS table of the fused gather's scatter: 4096 or 2048
     const double* seed = nullptr;  // device seed of f (nullptr means 1)
@@ -424,6 +438,7 @@ struct GroupDev {
     double* leaf_shadow[kGLeaves] = {};
     int32_t leaf_acc[kGLeaves] = {};
     GOp ops[kGOps];
+    uint32_t needed = 0;  // bit j: the reverse reads the value of op j (directly or through another op's)
     int32_t export_slot[kGExports] = {};
     double* export_val[kGExports] = {};
     const double* export_shadow[kGExports] = {};
@@ -433,6 +448,25 @@ struct GroupDev {
     int32_t* ticket = nullptr;
     double* f_out = nullptr;
 };
+
+// The reverse of a gather of n_elems rows of k entries (conn, coefficients B)
+// whose products lie in the order of the transposed connectivity: out[n]
+// (=|+=) sum of prod[offs[n] .. offs[n + 1]).  While *stale is 0; else conn is
+// no longer what that order was computed from, and B adj is scattered by
+// element with atomics.
+struct GatherRev {
+    int64_t n_nodes = 0, n_elems = 0;
+    int32_t k = 0;
+    const int32_t* offs = nullptr;
+    const double* prod = nullptr;
+    const int32_t* conn = nullptr;
+    const double* B = nullptr;
+    const double* adj = nullptr;
+    const int32_t* stale = nullptr;
+    double* out = nullptr;
+    int accumulate = 1;
+};
+hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s);
 
 enum GroupMode { G_FWD = 0, G_REV = 1, G_FWDREV = 2 };
 

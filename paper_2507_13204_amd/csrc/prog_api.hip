@@ -77,6 +77,13 @@ struct Group {
     int32_t pos = 0;      // schedule position: its last member (the end for a sum-only group)
     uint32_t hash_shift = kHashRotDefault;
     int agg_slots = 4096;
+    // Reverse of the gather through its transposed connectivity: room for it
+    // (planned, when the gather is large enough), and whether it is used
+    // (decided at bind from the connectivity).
+    size_t pos_off = NONE, offs_off = NONE, cursor_off = NONE, copy_off = NONE, adj_off = NONE,
+           prod_off = NONE, csr_scan_off = NONE;
+    bool gather_first = false;  // its delivery is the first into the operand's shadow
+    bool transposed = false;
 };
 
 // One step of the forward schedule: a non-pointwise construct or a group.
@@ -108,10 +115,36 @@ struct pg_prog_s {
     int64_t tape_bytes = 0;
     std::vector<size_t> input_shadow_off;  // internal shadows for inputs without a grad buffer
     char* ws = nullptr;
-    pg_prog_stats stats{};
+    pg_prog_stats planned_stats{}, stats{};  // as planned; with what bind decided
+    std::vector<char> stored_first;          // views whose first delivery turned out to store
 };
 
 namespace {
+
+// Incidences of a gather from which its reverse may go through the transposed
+// connectivity (below, the extra launches cost more than the atomics), and up
+// to which the plan keeps room for it (16 bytes and a share per incidence:
+// some 150 MB).
+constexpr int64_t kTransposeMin = 1 << 16, kTransposeMax = 1 << 23;
+// Incidences of one operand entry up to which one thread adds them.
+constexpr int32_t kTransposeDegree = 256;
+
+// Whether the sampled workgroups' scatter is one memory request for every
+// fourth incidence or more: a flush instruction costs a request per 128-byte
+// line of its 64 entries.
+bool scattered(const std::vector<std::vector<int32_t>>& tiles) {
+    int64_t lines = 0, incidences = 0;
+    std::vector<int32_t> l;
+    for (const auto& t : tiles) {
+        l.clear();
+        for (const int32_t n : t) l.push_back(n >> 4);
+        std::sort(l.begin(), l.end());
+        lines += std::unique(l.begin(), l.end()) - l.begin();
+        incidences += (int64_t)t.size();
+    }
+    return incidences > 0 && 4 * lines >= incidences;
+}
+
 
 pg_status add_view(pg_prog p, const Op& op, int32_t* view) {
     if (!p) return perr(PG_EINVAL, "program is NULL");
@@ -566,7 +599,10 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
                 if (g.leaves[l] == g.gather) continue;
                 la[l] = deliver(g.leaves[l], false);
             }
-            if (g.gather >= 0) deliver(ops[(size_t)g.gather].a, true);
+            if (g.gather >= 0) {
+                g.gather_first = !touched[(size_t)ops[(size_t)g.gather].a];
+                deliver(ops[(size_t)g.gather].a, true);
+            }
         } else {
             const Op& op = ops[(size_t)it.id];
             if (!op.active) continue;
@@ -602,10 +638,26 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
     for (const Op& op : ops)
         if (op.live && op.kind == P_SCAN) scan_chunks = std::max(scan_chunks, prog_scan_chunks(op.n));
     p->scan_off = scan_chunks ? take(sizeof(double) * (size_t)scan_chunks) : NONE;
+    // Transposed connectivity of the gathers that may be delivered through it.
+    for (Group& g : G) {
+        g.transposed = false;
+        g.pos_off = NONE;
+        if (g.gather < 0) continue;
+        const Op& op = ops[(size_t)g.gather];
+        const int64_t inc = op.n * op.k, nn = ops[(size_t)op.a].n;
+        if (!op.active || inc < kTransposeMin || inc > kTransposeMax) continue;
+        g.pos_off = take(sizeof(int32_t) * (size_t)inc);
+        g.prod_off = take(sizeof(double) * (size_t)inc);
+        g.copy_off = take(sizeof(int32_t) * (size_t)inc);
+        g.offs_off = take(sizeof(int32_t) * (size_t)(nn + 1));
+        g.cursor_off = take(sizeof(int32_t) * (size_t)nn);
+        g.adj_off = take(sizeof(double) * (size_t)op.n);
+        g.csr_scan_off = take(sizeof(int64_t) * (size_t)scan_scratch_items(nn));
+    }
     p->ws_bytes = off;
 
     // What the transformation produced.
-    pg_prog_stats& st = p->stats;
+    pg_prog_stats& st = p->planned_stats;
     st = pg_prog_stats{};
     for (const Item& it : p->sched) {
         if (it.group) {
@@ -638,6 +690,7 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
     }
     st.tape_bytes = p->tape_bytes;
     st.workspace_bytes = (int64_t)p->ws_bytes;
+    p->stats = st;
     p->planned = true;
     p->ws = nullptr;
     *workspace_bytes = p->ws_bytes;
@@ -668,8 +721,13 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
     }
     PG_HIP(hipMemcpy(&hflag, flag, sizeof hflag, hipMemcpyDeviceToHost));
     if (hflag) return perr(PG_ERANGE, "segment offsets are not 0 = o_0 <= ... <= o_n_seg = length");
-    // LDS table size and hash rotation of each fused gather's scatter, chosen
-    // on sampled workgroups.
+    // How each gather's reverse is delivered, decided on sampled workgroups:
+    // through the transposed connectivity where their entries share few cache
+    // lines, else scattered with the LDS table size and hash rotation chosen
+    // for them.
+    p->stats = p->planned_stats;
+    p->stored_first.assign(p->ops.size(), 0);
+    PG_HIP(launch_zero(flag + 3, sizeof(int32_t), nullptr));  // no connectivity changed yet
     for (Group& g : p->groups) {
         if (g.gather < 0) continue;
         const Op& op = p->ops[(size_t)g.gather];
@@ -691,6 +749,38 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
             cnt.push_back((int64_t)t.size());
         }
         if (tiles.empty()) continue;
+        g.transposed = false;
+        if (g.pos_off != NONE && scattered(tiles)) {
+            const int64_t inc = op.n * op.k, nn = p->ops[(size_t)op.a].n;
+            char* w = static_cast<char*>(ws);
+            int32_t* cursor = reinterpret_cast<int32_t*>(w + g.cursor_off);
+            int32_t* offs = reinterpret_cast<int32_t*>(w + g.offs_off);
+            int32_t* copy = reinterpret_cast<int32_t*>(w + g.copy_off);
+            // The structure comes from the copy alone, and is used while the
+            // connectivity is still equal to it.
+            PG_HIP(hipMemcpy(copy, op.conn, sizeof(int32_t) * (size_t)inc, hipMemcpyDeviceToDevice));
+            PG_HIP(launch_zero(cursor, sizeof(int32_t) * (size_t)nn, nullptr));
+            PG_HIP(launch_zero(flag + 2, sizeof(int32_t), nullptr));
+            PG_HIP(launch_validate_count(copy, inc, nn, cursor, flag, nullptr));
+            PG_HIP(launch_max(cursor, nn, flag + 2, nullptr));
+            int32_t degree = 0;
+            PG_HIP(hipMemcpy(&degree, flag + 2, sizeof degree, hipMemcpyDeviceToHost));
+            if (degree <= kTransposeDegree) {
+                PG_HIP(launch_exclusive_scan(cursor, nn, offs, reinterpret_cast<int64_t*>(w + g.csr_scan_off),
+                                             nullptr));
+                // the incidence list is needed only for its inverse: it is
+                // built where the products will be
+                int32_t* list = reinterpret_cast<int32_t*>(w + g.prod_off);
+                PG_HIP(launch_csr_fill_sort(copy, inc, nn, offs, cursor, list, nullptr));
+                PG_HIP(launch_invert(list, inc, reinterpret_cast<int32_t*>(w + g.pos_off), nullptr));
+                g.transposed = true;
+                if (g.gather_first) p->stored_first[(size_t)op.a] = 1;
+                --p->stats.atomic_ops;
+                ++p->stats.rescheduled_ops;
+                p->stats.rev_kernels += 2;
+                continue;
+            }
+        }
         choose_table(ptr.data(), cnt.data(), (int64_t)tiles.size(), &g.agg_slots, &g.hash_shift);
         // The smaller table only if no workgroup of the gather would probe in it.
         if (g.agg_slots == 2048) {
@@ -705,6 +795,7 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
             }
         }
     }
+    PG_HIP(hipStreamSynchronize(nullptr));  // what was built is there for runs on any stream
     p->ws = static_cast<char*>(ws);
     return PG_OK;
 }
@@ -776,6 +867,16 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
                 ++d.n_exports;
             }
         }
+        // Values the reverse reads: operands of products and maps, and what
+        // those are computed from.
+        for (int32_t m = d.n_ops - 1; m >= 0; --m) {
+            const GOp& o = d.ops[m];
+            const bool reads = o.kind == P_MAP || o.kind == P_MUL || (d.needed >> m & 1);
+            if (!reads) continue;
+            if (o.a >= d.n_leaves) d.needed |= 1u << (o.a - d.n_leaves);
+            if ((o.kind == P_MUL || o.kind == P_ADD) && o.b >= d.n_leaves)
+                d.needed |= 1u << (o.b - d.n_leaves);
+        }
         if (g.has_sum) {
             d.sum_slot = slot(p->sum_view);
             d.partials = partials;
@@ -795,6 +896,13 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
             d.gsrc_shadow = ops[(size_t)go.a].active ? shd[(size_t)go.a] : nullptr;
             d.hash_shift = g.hash_shift;
             d.agg_slots = g.agg_slots;
+            if (g.transposed) {
+                d.gather_adj = at(p, g.adj_off);
+                d.gather_prod = at(p, g.prod_off);
+                d.gather_pos = reinterpret_cast<const int32_t*>(p->ws + g.pos_off);
+                d.conn_copy = reinterpret_cast<const int32_t*>(p->ws + g.copy_off);
+                d.stale = reinterpret_cast<int32_t*>(p->ws + p->flag_off) + 3;
+            }
             if (g.export_gather) {
                 d.export_slot[d.n_exports] = d.gather_slot;
                 d.export_val[d.n_exports] = at(p, go.val_off);
@@ -821,10 +929,30 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
         return d;
     };
 
+    // After a group's reverse: its gather's delivery through the transposed connectivity.
+    auto deliver_transposed = [&](int32_t gi) -> hipError_t {
+        const Group& g = p->groups[(size_t)gi];
+        if (!g.transposed) return hipSuccess;
+        const Op& go = ops[(size_t)g.gather];
+        GatherRev r;
+        r.n_nodes = ops[(size_t)go.a].n;
+        r.n_elems = go.n;
+        r.k = go.k;
+        r.offs = reinterpret_cast<const int32_t*>(p->ws + g.offs_off);
+        r.prod = at(p, g.prod_off);
+        r.conn = go.conn;
+        r.B = go.B;
+        r.adj = at(p, g.adj_off);
+        r.stale = reinterpret_cast<const int32_t*>(p->ws + p->flag_off) + 3;
+        r.out = shd[(size_t)go.a];
+        r.accumulate = g.gather_first ? 0 : 1;
+        return launch_gather_rev(r, s);
+    };
+
     // Shadows that take atomic additions (and gradients nothing reaches) start at zero.
     if (rev)
         for (int32_t v : p->zero_views)
-            PG_HIP(launch_zero(shd[(size_t)v], sizeof(double) * (size_t)ops[(size_t)v].n, s));
+            if (!p->stored_first[(size_t)v]) PG_HIP(launch_zero(shd[(size_t)v], sizeof(double) * (size_t)ops[(size_t)v].n, s));
     // Forward pass; with fusion the sum group runs its reverse in the same pass.
     const bool fused_last = rev && p->fusion;
     int64_t n_partials = 0;
@@ -834,6 +962,7 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
             const GroupDev d = group_dev(it.id);
             if (it.id == p->sum_group) n_partials = group_blocks(n_sum, group_block_size(d, mode));
             PG_HIP(launch_group(d, mode, s));
+            if (mode == G_FWDREV) PG_HIP(deliver_transposed(it.id));
         } else {
             PG_HIP(launch_prog_fwd(op_dev(it.id), s));
         }
@@ -849,7 +978,10 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
             const GroupDev d = group_dev(it.id);
             bool any = d.gsrc_shadow != nullptr;
             for (int l = 0; l < d.n_leaves; ++l) any = any || d.leaf_shadow[l] != nullptr;
-            if (any) PG_HIP(launch_group(d, G_REV, s));
+            if (any) {
+                PG_HIP(launch_group(d, G_REV, s));
+                PG_HIP(deliver_transposed(it.id));
+            }
         } else {
             const Op& op = ops[(size_t)it.id];
             if (!op.active) continue;

@@ -14,7 +14,7 @@ namespace pg {
 
 namespace {
 
-constexpr int kBS = 256;
+constexpr int kBS = kGroupBlock;
 
 inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBS - 1) / kBS); }
 
@@ -55,6 +55,46 @@ k_r_stencil(int64_t n, const double* __restrict__ yb, ProgTaps taps, double* __r
         ab[j] += s;
     else
         ab[j] = s;
+}
+
+// The reverse of a gather whose products lie in the order of its transposed
+// connectivity: entry n adds its run of them, in ascending incidence order,
+// and stores the sum (or adds it to what is there).  Streams the products; a
+// stale plan only clears here what k_gather_scatter then adds to.  Random
+// rows of eight, 200,003 of them on 300,007 entries (1.6 M incidences): one
+// atomic per incidence bound the group at 121 us (13 G/s); the products'
+// stores and this pass take 28, against 35 for a pass that reads B and the
+// adjoint through the incidence list (500,000 rows on 10^6: 66 against 116).
+__global__ void __launch_bounds__(kBS) k_gather_rev(GatherRev r) {
+    constexpr int D = 8;
+    const int64_t n = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kBS + threadIdx.x;
+    if (n >= r.n_nodes) return;
+    if (*r.stale) {
+        if (!r.accumulate) r.out[n] = 0.0;
+        return;
+    }
+    const int32_t p0 = r.offs[n], p1 = r.offs[n + 1];
+    double s = 0.0;
+    for (int32_t p = p0; p < p1; p += D) {
+        double v[D];
+#pragma unroll
+        for (int q = 0; q < D; ++q) v[q] = p + q < p1 ? r.prod[p + q] : 0.0;
+#pragma unroll
+        for (int q = 0; q < D; ++q)
+            if (p + q < p1) s += v[q];
+    }
+    r.out[n] = r.accumulate ? r.out[n] + s : s;
+}
+
+// The same by element with atomics, for a connectivity changed since the
+// transposed one was built (nothing to do otherwise).
+__global__ void __launch_bounds__(kBS) k_gather_scatter(GatherRev r) {
+    if (!*r.stale) return;
+    for (int64_t e = (int64_t)blockIdx.x * kBS + threadIdx.x; e < r.n_elems;
+         e += (int64_t)gridDim.x * kBS) {
+        const double v = r.adj[e];
+        for (int j = 0; j < r.k; ++j) atomic_add_f64(r.out + r.conn[e * r.k + j], r.B[e * r.k + j] * v);
+    }
 }
 
 // ------------------------------------------------------------ prefix scan
@@ -275,14 +315,221 @@ struct GatherRow {
     double b[N];
 };
 
+// A gathered row of any length: four entries' loads are in flight at a time.
+__device__ __forceinline__ double gather_any(const GroupDev& g, int64_t i) {
+    const int k = g.gk;
+    const int32_t* c = g.gconn + i * k;
+    const double* b = g.gB + i * k;
+    double u = 0.0;
+    int j = 0;
+    for (; j + 4 <= k; j += 4) {
+        int32_t n[4];
+        double bv[4], xv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n[q] = c[j + q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bv[q] = b[j + q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xv[q] = g.gsrc[n[q]];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u += bv[q] * xv[q];
+    }
+    for (; j < k; ++j) u += b[j] * g.gsrc[c[j]];
+    return u;
+}
+
+// The products of a gathered row with its adjoint, at their places in the
+// transposed connectivity.
+template <int K>
+__device__ __forceinline__ void store_products(const GroupDev& g, int64_t i, const GatherRow<K>& row,
+                                               double ub) {
+    g.gather_adj[i] = ub;
+    bool changed = false;
+    if constexpr (K > 0) {
+        int32_t pos[K], was[K];
+        load_conn_row<double, K>(g.gather_pos, i, pos);
+        load_conn_row<double, K>(g.conn_copy, i, was);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            g.gather_prod[pos[j]] = row.b[j] * ub;
+            changed |= was[j] != row.c[j];
+        }
+    } else {
+        for (int j = 0; j < g.gk; ++j) {
+            const int64_t q = i * g.gk + j;
+            g.gather_prod[g.gather_pos[q]] = g.gB[q] * ub;
+            changed |= g.conn_copy[q] != g.gconn[q];
+        }
+    }
+    if (changed) *g.stale = 1;
+}
+
+// The last workgroup to take the ticket sums the partials of f.
+template <int BS>
+__device__ __forceinline__ void sum_by_last(const GroupDev& g, double* lds, int* last_wg) {
+    if (threadIdx.x == 0) {
+        __threadfence();  // this workgroup's partial before its ticket
+        *last_wg = atomicAdd(g.ticket, 1) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (*last_wg) {
+        __threadfence();  // every partial is visible
+        double v = 0.0;
+        for (int q = threadIdx.x; q < (int)gridDim.x; q += BS) v += g.partials[q];
+        v = block_sum<BS>(v, lds);
+        if (threadIdx.x == 0) {
+            *g.f_out = v;
+            *g.ticket = 0;
+        }
+    }
+}
+
+// A larger group that scatters nothing.  The slots live in LDS, one column of
+// BS entries per slot, so a run-time slot index is an address and the
+// interpreter is a short loop; every load (leaves, export shadows, shadows
+// that are added to, the ops) is issued before the first is waited for.  Bound
+// by the interpreter's latency up to some 10^5 entries, by memory above.
+//
+// K: fused gather row length (0 none, -1 generic).
+template <int K, int MODE>
+__global__ void __launch_bounds__(kBS) k_group_lds(GroupDev g) {
+    constexpr bool REV = MODE != G_FWD;
+    constexpr bool FWD = MODE != G_REV;
+    extern __shared__ double slots[];
+    constexpr int kOpWords = (int)(sizeof(GOp) / 4);
+    static_assert(kGOps * kOpWords <= kBS, "one word of the ops per thread");
+    __shared__ alignas(16) uint32_t op_words[kGOps * kOpWords];
+    const GOp* const ops = reinterpret_cast<const GOp*>(op_words);
+    __shared__ double lds[kBS / kWave];
+    __shared__ int last_wg;
+    const int tid = threadIdx.x;
+    const int64_t i = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kBS + tid;
+    const bool ok = i < g.n;
+    const int L = g.n_leaves, ns = L + g.n_ops;
+    double* const r = slots + tid;                      // forward values, slot s at r[s * kBS]
+    double* const a = slots + (int64_t)ns * kBS + tid;  // adjoints (REV)
+    uint32_t word = 0;
+    if (tid < g.n_ops * kOpWords) word = reinterpret_cast<const uint32_t*>(g.ops)[tid];
+    double lv[kGLeaves] = {};
+    [[maybe_unused]] double sv[kGLeaves] = {}, ev[kGExports] = {};
+    [[maybe_unused]] GatherRow<K> row;
+    if (ok) {
+        if constexpr (K > 0) {
+            double xv[K];
+            load_conn_row<double, K>(g.gconn, i, row.c);
+            load_b_row<K>(g.gB, i, row.b);
+#pragma unroll
+            for (int j = 0; j < K; ++j) xv[j] = g.gsrc[row.c[j]];
+#pragma unroll
+            for (int l = 0; l < kGLeaves; ++l)
+                if (l < L && l != g.gather_slot) lv[l] = g.leaf[l][i];
+            double u = 0.0;
+#pragma unroll
+            for (int j = 0; j < K; ++j) u += row.b[j] * xv[j];
+            r[g.gather_slot * kBS] = u;
+        } else {
+#pragma unroll
+            for (int l = 0; l < kGLeaves; ++l)
+                if (l < L && l != g.gather_slot) lv[l] = g.leaf[l][i];
+            if constexpr (K < 0) {
+                r[g.gather_slot * kBS] = gather_any(g, i);
+            }
+        }
+        if constexpr (REV) {
+#pragma unroll
+            for (int x = 0; x < kGExports; ++x)
+                if (x < g.n_exports && g.export_shadow[x]) ev[x] = g.export_shadow[x][i];
+#pragma unroll
+            for (int l = 0; l < kGLeaves; ++l)
+                if (l < L && g.leaf_shadow[l] && g.leaf_acc[l]) sv[l] = g.leaf_shadow[l][i];
+        }
+    }
+    if (tid < g.n_ops * kOpWords) op_words[tid] = word;
+    __syncthreads();
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    if (ok) {
+#pragma unroll
+        for (int l = 0; l < kGLeaves; ++l)
+            if (l < L && l != g.gather_slot) r[l * kBS] = lv[l];
+        for (int j = 0; j < g.n_ops; ++j) {
+            // the reverse recomputes only the values that it reads
+            if (!FWD && !(g.needed >> j & 1)) continue;
+            const GOp o = ops[j];
+            const int kind = uni(o.kind);
+            const double x = r[uni(o.a) * kBS];
+            double v;
+            if (kind == P_SCALE) {
+                v = o.alpha * x;
+            } else if (kind == P_MAP) {
+                v = map_f(uni(o.fn), x);
+            } else {
+                const double y = r[uni(o.b) * kBS];
+                v = kind == P_ADD ? o.alpha * x + o.beta * y : x * y;
+            }
+            r[(L + j) * kBS] = v;
+        }
+        if constexpr (FWD) {
+            for (int x = 0; x < g.n_exports; ++x) g.export_val[x][i] = r[g.export_slot[x] * kBS];
+        }
+    }
+    if constexpr (FWD) {
+        if (g.sum_slot >= 0) {
+            const double t = block_sum<kBS>(ok ? r[g.sum_slot * kBS] : 0.0, lds);
+            if (tid == 0) g.partials[blockIdx.x] = t;
+        }
+    }
+    if constexpr (REV) {
+        if (ok) {
+            for (int q = 0; q < ns; ++q) a[q * kBS] = 0.0;
+            if (g.sum_slot >= 0) a[g.sum_slot * kBS] = g.seed ? *g.seed : 1.0;
+#pragma unroll
+            for (int x = 0; x < kGExports; ++x)
+                if (x < g.n_exports && g.export_shadow[x]) a[g.export_slot[x] * kBS] += ev[x];
+            for (int j = g.n_ops - 1; j >= 0; --j) {
+                const GOp o = ops[j];
+                const int kind = uni(o.kind), oa = uni(o.a) * kBS;
+                const double yb = a[(L + j) * kBS];
+                if (kind == P_SCALE) {
+                    a[oa] += o.alpha * yb;
+                } else if (kind == P_MAP) {
+                    a[oa] += map_df(uni(o.fn), r[oa]) * yb;
+                } else {
+                    const int ob = uni(o.b) * kBS;
+                    if (kind == P_ADD) {
+                        a[oa] += o.alpha * yb;
+                        a[ob] += o.beta * yb;
+                    } else {
+                        const double av = r[oa], bv = r[ob];
+                        a[oa] += bv * yb;
+                        a[ob] += av * yb;
+                    }
+                }
+            }
+#pragma unroll
+            for (int l = 0; l < kGLeaves; ++l) {
+                if (l >= L || l == g.gather_slot || !g.leaf_shadow[l]) continue;
+                const double v = a[l * kBS];
+                g.leaf_shadow[l][i] = g.leaf_acc[l] ? sv[l] + v : v;
+            }
+            if constexpr (K != 0)
+                if (g.gather_adj) store_products<K>(g, i, row, a[g.gather_slot * kBS]);
+        }
+    }
+    if constexpr (FWD) {
+        if (g.sum_slot >= 0 && g.ticket) sum_by_last<kBS>(g, lds, &last_wg);
+    }
+}
+
 // K: fused gather row length (0 none, -1 generic); NS: slots; BS: workgroup;
-// S: slots of the LDS table of the fused gather's scatter (0 without one).
+// S: slots of the LDS table of the fused gather's scatter (0 without one: no
+// gather, a forward pass, or a gather whose adjoint is written to
+// g.gather_adj for the pass over the transposed connectivity).
 template <int K, int MODE, int BS, int NS, int S>
 __global__ void __launch_bounds__(BS) k_group(GroupDev g) {
     constexpr bool REV = MODE != G_FWD;
     constexpr bool FWD = MODE != G_REV;
-    constexpr bool AGG = REV && K != 0;
-    static_assert(AGG == (S > 0), "a table exactly when the reverse scatters a fused gather");
+    constexpr bool AGG = S > 0;
+    static_assert(!AGG || (REV && K != 0), "only the reverse of a fused gather scatters");
     constexpr int NL = NS < kGLeaves ? NS : kGLeaves;
     __shared__ double lds[BS / kWave];
     __shared__ int last_wg;
@@ -320,12 +567,12 @@ __global__ void __launch_bounds__(BS) k_group(GroupDev g) {
             for (int j = 0; j < K; ++j) u += row.b[j] * xv[j];
             r.set(g.gather_slot, u);
         } else if constexpr (K < 0) {
-            double u = 0.0;
-            for (int j = 0; j < g.gk; ++j) u += g.gB[i * g.gk + j] * g.gsrc[g.gconn[i * g.gk + j]];
-            r.set(g.gather_slot, u);
+            r.set(g.gather_slot, gather_any(g, i));
         }
         (void)values;
         for (int j = 0; j < g.n_ops; ++j) {
+            // the reverse recomputes only the values that it reads
+            if (!FWD && !(g.needed >> j & 1)) continue;
             const GOp o = g.ops[j];
             const double x = r.get(o.a);
             double v;
@@ -381,6 +628,9 @@ __global__ void __launch_bounds__(BS) k_group(GroupDev g) {
                     *p = a.r[l];
             }
         }
+        if constexpr (REV && K != 0 && !AGG) {
+            if (ok && g.gather_adj) store_products<K>(g, i, row, a.get(g.gather_slot));
+        }
         if constexpr (AGG) {
             if (scatter) {
                 // The table is cleared only now, so the loads above were not held up.
@@ -405,57 +655,68 @@ __global__ void __launch_bounds__(BS) k_group(GroupDev g) {
         }
     }
     if constexpr (FWD) {
-        if (g.sum_slot >= 0 && g.ticket) {
-            if (threadIdx.x == 0) {
-                __threadfence();  // this workgroup's partial before its ticket
-                last_wg = atomicAdd(g.ticket, 1) == (int)gridDim.x - 1;
-            }
-            __syncthreads();
-            if (last_wg) {
-                __threadfence();  // every partial is visible
-                double v = 0.0;
-                for (int q = threadIdx.x; q < (int)gridDim.x; q += BS) v += g.partials[q];
-                v = block_sum<BS>(v, lds);
-                if (threadIdx.x == 0) {
-                    *g.f_out = v;
-                    *g.ticket = 0;
-                }
-            }
-        }
+        if (g.sum_slot >= 0 && g.ticket) sum_by_last<BS>(g, lds, &last_wg);
     }
 }
 
+// Whether a launch scatters its fused gather with atomics (an inactive
+// operand, or one delivered through the transposed connectivity, does not).
+bool group_scatters(const GroupDev& g, int mode) {
+    return g.gather_slot >= 0 && mode != G_FWD && g.gsrc_shadow && !g.gather_adj;
+}
+
 template <int K, int NS>
-hipError_t launch_group_k(const GroupDev& g, int mode, hipStream_t s) {
-    constexpr int BS = kGroupBlock, BSS = K != 0 ? kGroupBlockScatter : kGroupBlock;
-    constexpr int SB = K != 0 ? kAggSlots : 0, SS = K != 0 ? kAggSlotsSmall : 0;
+hipError_t launch_scatter(const GroupDev& g, int mode, hipStream_t s) {
+    constexpr int BS = kGroupBlockScatter;
     const dim3 grid((unsigned)group_blocks(g.n, BS)), block(BS);
-    const dim3 grid_s((unsigned)group_blocks(g.n, BSS)), block_s(BSS);
     const bool small = g.agg_slots == kAggSlotsSmall;
-    switch (mode) {
-        case G_FWD: PG_LAUNCH((k_group<K, G_FWD, BS, NS, 0>), grid, block, 0, s, g); break;
-        case G_REV:
-            if (small)
-                PG_LAUNCH((k_group<K, G_REV, BSS, NS, SS>), grid_s, block_s, 0, s, g);
-            else
-                PG_LAUNCH((k_group<K, G_REV, BSS, NS, SB>), grid_s, block_s, 0, s, g);
-            break;
-        default:
-            if (small)
-                PG_LAUNCH((k_group<K, G_FWDREV, BSS, NS, SS>), grid_s, block_s, 0, s, g);
-            else
-                PG_LAUNCH((k_group<K, G_FWDREV, BSS, NS, SB>), grid_s, block_s, 0, s, g);
-            break;
+    if (mode == G_REV) {
+        if (small)
+            PG_LAUNCH((k_group<K, G_REV, BS, NS, kAggSlotsSmall>), grid, block, 0, s, g);
+        else
+            PG_LAUNCH((k_group<K, G_REV, BS, NS, kAggSlots>), grid, block, 0, s, g);
+    } else {
+        if (small)
+            PG_LAUNCH((k_group<K, G_FWDREV, BS, NS, kAggSlotsSmall>), grid, block, 0, s, g);
+        else
+            PG_LAUNCH((k_group<K, G_FWDREV, BS, NS, kAggSlots>), grid, block, 0, s, g);
     }
     return hipGetLastError();
 }
 
+// Slots up to which a group that scatters nothing keeps them in registers.
+// In LDS, with more, the mix program's five-op reverse takes 6.7 us at
+// 300,007 entries (12.1 in registers) and the segment program's sum group 18.5
+// at 10^6 (20.8); its one-op reverse would take 13.0 (9.9 in registers).
+constexpr int kRegisterSlots = 4;
+
 template <int K>
 hipError_t launch_group_ns(const GroupDev& g, int mode, hipStream_t s) {
     const int need = g.n_leaves + g.n_ops;
-    if (need <= 4) return launch_group_k<K, 4>(g, mode, s);
-    if (need <= 8) return launch_group_k<K, 8>(g, mode, s);
-    return launch_group_k<K, 16>(g, mode, s);
+    if constexpr (K != 0) {
+        if (group_scatters(g, mode)) {
+            if (need <= 4) return launch_scatter<K, 4>(g, mode, s);
+            if (need <= 8) return launch_scatter<K, 8>(g, mode, s);
+            return launch_scatter<K, 16>(g, mode, s);
+        }
+    }
+    const dim3 grid((unsigned)group_blocks(g.n, kBS)), block(kBS);
+    if (need <= kRegisterSlots) {
+        constexpr int NS = kRegisterSlots;
+        switch (mode) {
+            case G_FWD: PG_LAUNCH((k_group<K, G_FWD, kBS, NS, 0>), grid, block, 0, s, g); break;
+            case G_REV: PG_LAUNCH((k_group<K, G_REV, kBS, NS, 0>), grid, block, 0, s, g); break;
+            default: PG_LAUNCH((k_group<K, G_FWDREV, kBS, NS, 0>), grid, block, 0, s, g); break;
+        }
+        return hipGetLastError();
+    }
+    const unsigned lds = (unsigned)(sizeof(double) * need * kBS * (mode == G_FWD ? 1 : 2));
+    switch (mode) {
+        case G_FWD: PG_LAUNCH((k_group_lds<K, G_FWD>), grid, block, lds, s, g); break;
+        case G_REV: PG_LAUNCH((k_group_lds<K, G_REV>), grid, block, lds, s, g); break;
+        default: PG_LAUNCH((k_group_lds<K, G_FWDREV>), grid, block, lds, s, g); break;
+    }
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -466,7 +727,7 @@ int64_t group_blocks(int64_t n, int bs) { return (n + bs - 1) / bs; }
 // pass; a larger workgroup combines more contributions per table clear and
 // flush (512 threads measured best for eight-node rows, as for the mesh).
 int group_block_size(const GroupDev& g, int mode) {
-    return (g.gather_slot >= 0 && mode != G_FWD) ? kGroupBlockScatter : kGroupBlock;
+    return group_scatters(g, mode) ? kGroupBlockScatter : kGroupBlock;
 }
 
 hipError_t launch_group(const GroupDev& g, int mode, hipStream_t s) {
@@ -486,6 +747,14 @@ hipError_t launch_group(const GroupDev& g, int mode, hipStream_t s) {
         }
     }
     return launch_group_ns<-1>(g, mode, s);
+}
+
+hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s) {
+    if (r.n_nodes == 0) return hipSuccess;
+    const dim3 grid(nblocks(r.n_nodes)), block(kBS);
+    PG_LAUNCH(k_gather_rev, grid, block, 0, s, r);
+    hipLaunchKernelGGL(k_gather_scatter, dim3(std::min(nblocks(r.n_elems), 256u)), block, 0, s, r);
+    return hipGetLastError();
 }
 
 hipError_t launch_prog_fwd(const ProgOpDev& o, hipStream_t s) {

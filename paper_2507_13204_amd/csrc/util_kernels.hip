@@ -120,6 +120,17 @@ k_validate_count(const int32_t* __restrict__ conn, int64_t n_items, int64_t n_no
     if (bad) atomicOr(flag, 1);
 }
 
+__global__ void __launch_bounds__(256)
+k_max(const int32_t* __restrict__ v, int64_t n, int32_t* __restrict__ out) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int32_t m = INT32_MIN;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        m = max(m, v[i]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = max(m, __shfl_xor(m, off, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(out, m);
+}
+
 // One workgroup per element-pass workgroup: its node numbers are put in
 // their home slots of an S-slot table; an insert that finds another node
 // there is counted (any two distinct nodes of a workgroup that share a home
@@ -255,6 +266,14 @@ k_csr_sort_rows(const int32_t* __restrict__ offs, int64_t n_nodes, int32_t* __re
         inc[b + 1] = key;
     }
 }
+
+__global__ void __launch_bounds__(256)
+k_invert(const int32_t* __restrict__ inc, int64_t n, int32_t* __restrict__ pos) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride)
+        pos[inc[q]] = (int32_t)q;
+}
+
 inline unsigned stream_grid(int64_t n, int per_block, int cap = 4096) {
     int64_t g = (n + per_block - 1) / per_block;
     if (g < 1) g = 1;
@@ -343,6 +362,18 @@ hipError_t launch_table_check(const int32_t* conn, int64_t n_elems, int32_t k, i
                            k, span, shift, miss);
     else
         return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_max(const int32_t* v, int64_t n, int32_t* out, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_max, dim3(stream_grid(n, 256 * 8, 1024)), dim3(256), 0, s, v, n, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_invert(const int32_t* inc, int64_t n, int32_t* pos, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_invert, dim3(stream_grid(n, 256 * 8, 8192)), dim3(256), 0, s, inc, n, pos);
     return hipGetLastError();
 }
 
