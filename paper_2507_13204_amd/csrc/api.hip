@@ -87,8 +87,9 @@ constexpr int kHashSamples = 64;
 // Probe count of an S-slot table with rotation `shift` on the sampled tiles
 // (an insert that finds no slot within kProbe steps counts 4 * kProbe: it
 // goes to a global atomic); stops early past `stop_at`.
+// *distinct (when not null): entries that took a slot or found none.
 int64_t table_cost(const int32_t* const* tiles, const int64_t* counts, int64_t n_tiles, int slots,
-                   uint32_t shift, int64_t stop_at) {
+                   uint32_t shift, int64_t stop_at, int64_t* distinct = nullptr) {
     constexpr int kProbe = 64;
     std::vector<int32_t> key((size_t)slots);
     const uint32_t mask = (uint32_t)slots - 1;
@@ -104,6 +105,7 @@ int64_t table_cost(const int32_t* const* tiles, const int64_t* counts, int64_t n
                 h = (h + 1) & mask;
                 ++probe;
             }
+            if (distinct && (probe == kProbe || key[h] == -1)) ++*distinct;
             if (probe == kProbe) {
                 cost += 4 * kProbe;
             } else {
@@ -160,6 +162,7 @@ struct pg_plan_s {
     int64_t mesh_blocks_n = 0;
     uint32_t hash_shift = kHashRotDefault;  // LDS table hash parameter chosen at bind time
     int agg_slots = 4096;        // LDS table size chosen at bind time
+    bool combine = true;         // whether combining in the table pays (bind time)
     // colour classes: elements of colour c are elist[colour_off[c] .. colour_off[c+1])
     std::vector<int64_t> colour_off;
     size_t o_elist = NONE;
@@ -529,7 +532,7 @@ MeshPass base_pass(pg_plan p, const void* x) {
     q.partials = p->at<double>(p->o_partials);
     q.block = p->opt.block;
     q.ept = p->opt.tile;
-    q.combine = p->opt.scatter != 1;
+    q.combine = p->opt.scatter != 1 && p->combine;
     q.hash_shift = p->hash_shift;
     q.agg_slots = p->agg_slots;
     return q;
@@ -762,6 +765,25 @@ uint32_t shift_of(const std::vector<std::vector<int32_t>>& tiles) {
         cnt.push_back((int64_t)t.size());
     }
     return choose_hash_shift(ptr.data(), cnt.data(), (int64_t)tiles.size(), 4096, nullptr);
+}
+
+// Whether combining in the chosen table pays: the probes it takes on the
+// sampled workgroups against the atomics it saves (entries less distinct
+// nodes).  Random meshes, 100,000 rows, FP64 gradient (table / direct, us):
+// rows of four, 14,000 nodes 24.0 / 27.1 (4.6 probes per atomic saved), 20,000
+// nodes 31.6 / 24.6 (6.9); rows of eight, 8,000 nodes 41.9 / 41.7 (3.9), 6,000
+// nodes 55.2 / 51.8 (7.9), 20,000 nodes 69.6 / 42.4 (50).
+bool combining_pays(const std::vector<std::vector<int32_t>>& tiles, int slots, uint32_t shift) {
+    // every eighth sampled workgroup: the sample decides more than it measures
+    int64_t probes = 0, saved = 0;
+    for (size_t i = 0; i < tiles.size(); i += 8) {
+        const int32_t* t = tiles[i].data();
+        const int64_t n = (int64_t)tiles[i].size();
+        int64_t distinct = 0;
+        probes += table_cost(&t, &n, 1, slots, shift, INT64_MAX, &distinct);
+        saved += n - distinct;
+    }
+    return probes <= 6 * saved;
 }
 
 void table_of(const std::vector<std::vector<int32_t>>& tiles, int* slots, uint32_t* shift) {
@@ -1058,6 +1080,7 @@ pg_status mesh_bind(pg_plan p, hipStream_t s) {
                 p->hash_shift = shift_of(tiles);
             }
         }
+        p->combine = p->opt.scatter != 0 || combining_pays(tiles, p->agg_slots, p->hash_shift);
         if (p->opt.scatter >= 2) {  // the caller fixed the table size
             p->agg_slots = p->opt.scatter == 2 ? 4096 : 2048;
             std::vector<const int32_t*> ptr;
@@ -1789,7 +1812,7 @@ pg_status pg_plan_info(pg_plan p, pg_plan_info_t* info) {
     r.block = p->opt.block;
     r.tile = p->opt.tile;
     const bool table = (p->kind == K_MESH || p->kind == K_BATCH) && p->opt.adjoint == PG_ADJ_ATOMIC &&
-                       p->opt.scatter != 1;
+                       p->opt.scatter != 1 && p->combine;
     r.lds_slots = table && p->bound ? (p->kind == K_BATCH ? 4096 : p->agg_slots) : 0;
     if (p->kind == K_MESH && p->opt.adjoint == PG_ADJ_TILED && p->bound)
         r.lds_slots = p->tiled_round_slots;

@@ -60,7 +60,29 @@ k_batch_tiles(BatchView bv, BatchPass p) {
     }
 }
 
-// Runtime k: one element per thread, rows streamed through the cache.
+// Runtime k <= KM: one element per thread, its row in registers.
+template <typename T, int KM, int MODE, int AGG>
+__global__ void __launch_bounds__(1024)
+k_batch_tiles_any(BatchView bv, BatchPass p) {
+    __shared__ double lds[16];
+    __shared__ AggOf<AGG> agg;
+    AggOf<AGG>* tab = nullptr;
+    if constexpr (AGG > 0) tab = &agg;
+    const TileRec r = load_tile(bv.tiles, xcd_remap(blockIdx.x, gridDim.x));
+    const int64_t inst = r.slot_inst >> 40;
+    double fb = 1.0;
+    if constexpr (has_rev(MODE)) fb = p.fbar ? p.fbar[inst] : 1.0;
+    TileArgs a{bv.conn, bv.B, bv.w, p.x, nullptr, p.u_in, p.u_store, nullptr,
+               static_cast<double*>(p.grad), nullptr, (uint32_t)(r.shift_noff >> 40), 0u};
+    const double tsum =
+        elem_any<T, KM, MODE, AGG>(a, bv.k, r.first, r.end, r.shift_noff & kNoffMask, fb, tab);
+    if constexpr (has_obj(MODE)) {
+        const double s = block_sum_dyn(tsum, lds);
+        if (threadIdx.x == 0) p.partials[r.slot_inst & kSlotMask] = s;
+    }
+}
+
+// Longer rows: one element per thread, streamed through the cache.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(1024)
 k_batch_tiles_dyn(BatchView bv, BatchPass p) {
@@ -108,6 +130,19 @@ hipError_t launch_agg(const BatchView& b, const BatchPass& p, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename T, int KM, int MODE>
+hipError_t launch_any(const BatchView& b, const BatchPass& p, hipStream_t s) {
+    const dim3 grid((unsigned)b.n_tiles), block(p.block);
+    if constexpr (is_atomic(MODE)) {
+        if (p.combine && (int64_t)p.block * b.k <= 2 * kAggSlots) {
+            PG_LAUNCH((k_batch_tiles_any<T, KM, MODE, kAggSlots>), grid, block, 0, s, b, p);
+            return hipGetLastError();
+        }
+    }
+    PG_LAUNCH((k_batch_tiles_any<T, KM, MODE, 0>), grid, block, 0, s, b, p);
+    return hipGetLastError();
+}
+
 template <typename T, int K, int MODE>
 hipError_t launch_ept(const BatchView& b, const BatchPass& p, hipStream_t s) {
     switch (b.tile_elems / p.block) {
@@ -126,6 +161,8 @@ hipError_t launch_k(const BatchView& b, const BatchPass& p, hipStream_t s) {
         case 2: return launch_ept<T, 2, MODE>(b, p, s);
         default:
             if (b.tile_elems != p.block) return hipErrorInvalidValue;
+            if (b.k <= 8) return launch_any<T, 8, MODE>(b, p, s);
+            if (b.k <= kAnyRow) return launch_any<T, kAnyRow, MODE>(b, p, s);
             PG_LAUNCH((k_batch_tiles_dyn<T, MODE>), dim3((unsigned)b.n_tiles), dim3(p.block), 0, s, b, p);
             return hipGetLastError();
     }

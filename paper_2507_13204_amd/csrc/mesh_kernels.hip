@@ -47,8 +47,30 @@ k_mesh_elem(MeshView m, MeshPass p) {
     }
 }
 
-// Runtime k (any 1 <= k <= 32): rows are streamed twice (forward, reverse)
-// through the cache instead of held in registers.
+// Runtime k <= KM: rows in registers, one element per thread.
+template <typename T, int KM, int MODE, int AGG>
+__global__ void __launch_bounds__(1024)
+k_mesh_elem_any(MeshView m, MeshPass p) {
+    __shared__ double lds[16];
+    __shared__ AggOf<AGG> agg;
+    const int64_t n_items = p.elist ? p.elist_n : m.n_elems;
+    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    double fb = 1.0;
+    if constexpr (has_rev(MODE)) fb = p.fbar ? p.fbar[0] : 1.0;
+    TileArgs a{m.conn, m.B, m.w, p.x, p.xd, p.u_in, p.u_store, p.v_out, p.gacc, p.elist,
+               p.hash_shift, buffer_bytes<T>(m.n_nodes)};
+    AggOf<AGG>* tab = nullptr;
+    if constexpr (AGG > 0) tab = &agg;
+    const double tsum =
+        elem_any<T, KM, MODE, AGG>(a, m.k, (int64_t)lb * blockDim.x, n_items, 0, fb, tab);
+    if constexpr (has_sum(MODE)) {
+        const double s = block_sum_dyn(tsum, lds);
+        if (threadIdx.x == 0) p.partials[p.partial_base + lb] = s;
+    }
+}
+
+// Longer rows (up to 32 entries): streamed twice (forward, reverse) through
+// the cache instead of held in registers.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(1024)
 k_mesh_elem_dyn(MeshView m, MeshPass p) {
@@ -161,11 +183,30 @@ hipError_t launch_elem_t(const MeshView& m, const MeshPass& p, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename T, int KM, int MODE>
+hipError_t launch_elem_any(const MeshView& m, const MeshPass& p, int64_t nb, hipStream_t s) {
+    const dim3 grid((unsigned)nb), block(p.block);
+    if constexpr (is_atomic(MODE)) {
+        const bool agg = p.combine && (int64_t)p.block * m.k <= 2 * kAggSlots;
+        if (agg && p.agg_slots == kAggSlotsSmall)
+            PG_LAUNCH((k_mesh_elem_any<T, KM, MODE, kAggSlotsSmall>), grid, block, 0, s, m, p);
+        else if (agg)
+            PG_LAUNCH((k_mesh_elem_any<T, KM, MODE, kAggSlots>), grid, block, 0, s, m, p);
+        else
+            PG_LAUNCH((k_mesh_elem_any<T, KM, MODE, 0>), grid, block, 0, s, m, p);
+    } else {
+        PG_LAUNCH((k_mesh_elem_any<T, KM, MODE, 0>), grid, block, 0, s, m, p);
+    }
+    return hipGetLastError();
+}
+
 template <typename T, int MODE>
 hipError_t launch_elem_dyn_t(const MeshView& m, const MeshPass& p, hipStream_t s) {
     const int64_t n_items = p.elist ? p.elist_n : m.n_elems;
     const int64_t nb = mesh_blocks(n_items, p.block, 1);
     if (nb == 0) return hipSuccess;
+    if (m.k <= 8) return launch_elem_any<T, 8, MODE>(m, p, nb, s);
+    if (m.k <= kAnyRow) return launch_elem_any<T, kAnyRow, MODE>(m, p, nb, s);
     PG_LAUNCH((k_mesh_elem_dyn<T, MODE>), dim3((unsigned)nb), dim3(p.block), 0, s, m, p);
     return hipGetLastError();
 }

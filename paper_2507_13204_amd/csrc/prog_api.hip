@@ -135,7 +135,8 @@ constexpr int32_t kTransposeDegree = 256;
 bool scattered(const std::vector<std::vector<int32_t>>& tiles) {
     int64_t lines = 0, incidences = 0;
     std::vector<int32_t> l;
-    for (const auto& t : tiles) {
+    for (size_t i = 0; i < tiles.size(); i += 8) {  // every eighth: it decides more than it measures
+        const auto& t = tiles[i];
         l.clear();
         for (const int32_t n : t) l.push_back(n >> 4);
         std::sort(l.begin(), l.end());
