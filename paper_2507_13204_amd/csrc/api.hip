@@ -589,6 +589,15 @@ SmallPass small_pass(pg_plan p) {
     return sp;
 }
 
+// Lets the element pass sum f itself (through the ticket in the flag words)
+// where its grid is small enough; an empty mesh launches nothing.
+bool sum_in_pass(pg_plan p, MeshPass& q, double* f_out) {
+    if (p->mesh_blocks_n == 0 || p->mesh_blocks_n > kTicketBlocks) return false;
+    q.ticket = p->at<int32_t>(p->o_flag) + 2;  // zeroed at bind
+    q.f_out = f_out;
+    return true;
+}
+
 pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, double* f_out,
                    int want, const CallTape& t, hipStream_t s) {
     const MeshView& m = p->mesh;
@@ -630,10 +639,11 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
     }
     if (!grd) {
         q.u_store = t.out ? static_cast<double*>(t.out) : p->at<double>(p->o_u);
+        const bool ticket = f_out && sum_in_pass(p, q, f_out);
         PG_HIP(tkern(p, true));
         PG_HIP(launch_mesh_elem(m, M_PRIMAL, q, s));
         PG_HIP(tkern(p, false));
-        if (f_out) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, f_out, s));
+        if (f_out && !ticket) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, f_out, s));
         if (!t.out && q.u_store) {
             p->tape_valid = true;
             p->tape_x = x;
@@ -696,9 +706,8 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
         const TiledView tv = tiled_view(p);
         PG_HIP(tmark(p, 1, true, s));
         PG_HIP(launch_mesh_tiled(m, q, tv, obj, s));
-        PG_HIP(launch_node_tiled(m, tv, grad, acc, s));
+        PG_HIP(launch_node_tiled(m, tv, grad, acc, q.partials, p->tiled_nt, obj ? f_out : nullptr, s));
         PG_HIP(tmark(p, 1, false, s));
-        if (obj && f_out) PG_HIP(launch_final_sum(q.partials, p->tiled_nt, f_out, s));
         return PG_OK;
     }
     if (p->opt.adjoint == PG_ADJ_GATHER) {
@@ -706,7 +715,8 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
         PG_HIP(tmark(p, 1, true, s));
         PG_HIP(launch_mesh_elem(m, obj ? M_GRAD_V : M_ADJ_V, q, s));
         PG_HIP(launch_mesh_node_gather(m, p->at<int32_t>(p->o_offs), p->at<int32_t>(p->o_inc),
-                                       p->at<char>(p->o_binc), q.v_out, grad, acc, 256, s));
+                                       p->at<char>(p->o_binc), q.v_out, grad, acc, 256, q.partials,
+                                       p->mesh_blocks_n, obj ? f_out : nullptr, s));
         PG_HIP(tmark(p, 1, false, s));
     } else {  // atomic
         if (f32) {
@@ -715,6 +725,7 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
             q.gacc = static_cast<double*>(grad);
             if (!acc) PG_HIP(launch_zero(grad, sizeof(double) * (size_t)m.n_nodes, s));
         }
+        const bool ticket = !f32 && obj && f_out && sum_in_pass(p, q, f_out);
         PG_HIP(tkern(p, true));
         PG_HIP(launch_mesh_elem(m, obj ? M_GRAD_ATOMIC : M_ADJ_ATOMIC, q, s));
         PG_HIP(tkern(p, false));
@@ -723,10 +734,9 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
                                          q.partials, p->mesh_blocks_n, f_out, s));
         else if (f32)
             PG_HIP(launch_f64_to_f32(q.gacc, static_cast<float*>(grad), m.n_nodes, acc, 1, s));
-        if (!f32 && obj && f_out) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, f_out, s));
-        return PG_OK;
+        if (!f32 && obj && f_out && !ticket)
+            PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, f_out, s));
     }
-    if (obj && f_out) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, f_out, s));
     return PG_OK;
 }
 
@@ -1291,13 +1301,13 @@ pg_status bdense_run(pg_plan p, const void* X, const double* fbar, void* G, doub
         // a tape recorded from another X is gone.
         PG_HIP(launch_bdense_fwd(p->bd, X, partials, V, s));
         p->tape_valid = false;
-        if (obj && f_out) PG_HIP(launch_final_sum(partials, p->bd_tiles, f_out, s));
     } else {
         pg_status ts = stored_tape_ok(p, X);
         if (ts) return ts;
     }
     PG_HIP(tkern(p, true));
-    PG_HIP(launch_bdense_bwd(p->bd, Vin, fbar, G, p->opt.accumulate, s));
+    PG_HIP(launch_bdense_bwd(p->bd, Vin, fbar, G, p->opt.accumulate, partials, p->bd_tiles,
+                             obj ? f_out : nullptr, s));
     PG_HIP(tkern(p, false));
     return PG_OK;
 }
@@ -1780,8 +1790,9 @@ pg_status pg_jvp(pg_plan p, const void* x, const void* d, double* jvp_out, pg_st
         PG_HIP(launch_mesh_small(p->mesh, M_JVP, q, sp, s));
         return PG_OK;
     }
+    const bool ticket = sum_in_pass(p, q, jvp_out);
     PG_HIP(launch_mesh_elem(p->mesh, M_JVP, q, s));
-    PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, jvp_out, s));
+    if (!ticket) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, jvp_out, s));
     return PG_OK;
 }
 

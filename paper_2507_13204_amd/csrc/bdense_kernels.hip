@@ -3,11 +3,12 @@
 //   backward  G = fbar * A^T V
 //
 // Both products are m x m by m x n contractions on the matrix cores.  FP64:
-// v_mfma_f64_16x16x4_f64.  FP32: each operand is split into three bfloat16
-// parts (8 + 8 + 8 bits, nearest) and the six products that reach FP32
-// precision run on v_mfma_f32_16x16x32_bf16, smallest first; every 32 terms
-// the FP32 result is added into FP64 accumulators and the matrix-core
-// accumulators restart from zero, so every longer accumulation is FP64.  A wave
+// v_mfma_f64_16x16x4_f64.  FP32, small: v_mfma_f32_16x16x4_f32, 16 terms at a
+// time.  FP32, large: each operand is split into three bfloat16 parts (8 + 8 +
+// 8 bits, nearest) and the six products that reach FP32 precision run on
+// v_mfma_f32_16x16x32_bf16, smallest first, 32 terms at a time.  Either FP32
+// sum is added into FP64 accumulators and the next starts from zero, so every
+// longer accumulation is FP64.  A wave
 // loads its operand fragments from global memory straight into the registers
 // the instruction reads, a k-step or more ahead, so there is no LDS staging
 // and no barrier in the k loop; the nonlinearity and its derivative are fused
@@ -26,15 +27,22 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
-// E: consecutive k a lane holds of a k-step of 4 E (lane group lk = lane / 16
-// holds k = E lk + e).
+// The arithmetic of a product.
+enum Arith {
+    FP64 = 0,   // v_mfma_f64_16x16x4_f64
+    FP32 = 1,   // v_mfma_f32_16x16x4_f32, 16 terms to a sum
+    SPLIT = 2,  // FP32 operands in three bfloat16 parts, 32 terms to a sum
+};
+
 template <typename T>
 struct Mfma;
 
 template <>
 struct Mfma<double> {
     using acc_t = d4;
-    static constexpr int E = 4;
+    __device__ static acc_t mac(double a, double b, acc_t c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
     // Output row (within the 16 x 16 block) of register r in lanes 16*g .. 16*g+15.
     __device__ static int row(int g, int r) { return g + 4 * r; }
 };
@@ -42,7 +50,9 @@ struct Mfma<double> {
 template <>
 struct Mfma<float> {
     using acc_t = f4;
-    static constexpr int E = 8;
+    __device__ static acc_t mac(float a, float b, acc_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
     __device__ static int row(int g, int r) { return 4 * g + r; }
 };
 
@@ -124,10 +134,10 @@ struct Shape {
 };
 
 // One k-step of both operands as a lane holds them.
-template <typename T, int BX, int BY>
+template <typename T, int E, int BX, int BY>
 struct Frag {
-    T a[Mfma<T>::E][BX];
-    T b[Mfma<T>::E][BY];
+    T a[E][BX];
+    T b[E][BY];
 };
 
 // C[M x N] = op(A)[M x K] * Bm[K x N].
@@ -146,23 +156,36 @@ struct Frag {
 // instructions of the split and the FP64 sums in FP32 (118 TFLOP/s, 100 on
 // v_mfma_f32_16x16x4_f32 through LDS), and by latency below some 500 x 500:
 // 257 x 129 takes 13 us per gradient (106 / 81 before, in 128 x 128 tiles).
-template <typename T, bool TRANS_A, int EPI, typename S>
+template <typename T, int AR, bool TRANS_A, int EPI, typename S>
 __global__ void __launch_bounds__(S::NTHR, S::OCC)
 k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_t N, int64_t K,
             const T* __restrict__ W, double* __restrict__ partials, T* __restrict__ Vout,
-            const double* __restrict__ fbar, T* __restrict__ Gout, int accumulate, int tiles_n) {
+            const double* __restrict__ fbar, T* __restrict__ Gout, int accumulate, int tiles_n,
+            int64_t np, double* __restrict__ f_out) {
     using MF = Mfma<T>;
     using acc_t = typename MF::acc_t;
     constexpr int BX = S::BX, BY = S::BY, D = S::template D<T>, KW = S::KW;
-    constexpr int E = MF::E, KS = 4 * E;  // k per lane and per step
-    constexpr bool kWide = std::is_same<T, float>::value;
-    using F = Frag<T, BX, BY>;
-    __shared__ double red[S::NWAVES];
+    static_assert((AR == FP64) == (sizeof(T) == 8), "FP64 arithmetic for FP64 operands");
+    // A k-step is 4 E deep; a lane (li, lk) holds E of them: consecutive ones,
+    // or, for the FP32 instruction, every fourth, so that a 16-term sum takes
+    // its terms in ascending k.
+    constexpr int E = AR == SPLIT ? 8 : 4, KS = 4 * E;
+    constexpr int kBase = AR == FP32 ? 1 : E, kStep = AR == FP32 ? 4 : 1;
+    constexpr bool kWide = AR != FP64;
+    using F = Frag<T, E, BX, BY>;
+    __shared__ double red[16];
+    // Backward: a workgroup past the tiles sums the forward's partials of f.
+    const uint32_t tiles = gridDim.x - (EPI == EPI_BWD && f_out ? 1 : 0);
+    if (EPI == EPI_BWD && blockIdx.x == tiles) {
+        const double f = final_sum_block<false>(partials, np, red);
+        if (threadIdx.x == 0) f_out[0] = f;
+        return;
+    }
 
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int wmn = wid % (S::WM * S::WN), kw = wid / (S::WM * S::WN);
-    const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t tile = xcd_remap(blockIdx.x, tiles);
     // First row / column of wave block q, and of the whole block it reads.
     const int64_t ti = (int64_t)(tile / tiles_n) * S::TM, tj = (int64_t)(tile % tiles_n) * S::TN;
     auto own_i = [&](int q) { return ti + (q / S::WN) * (16 * BX); };
@@ -180,14 +203,14 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
 
     const T* pa[TRANS_A ? 1 : BX];
     if constexpr (TRANS_A) {
-        pa[0] = A + low(i0 + BX * li, M - BX) + (kbeg + E * lk) * M;
+        pa[0] = A + low(i0 + BX * li, M - BX) + (kbeg + kBase * lk) * M;
     } else {
 #pragma unroll
-        for (int x = 0; x < BX; ++x) pa[x] = A + low(i0 + 16 * x + li, M - 1) * K + (kbeg + E * lk);
+        for (int x = 0; x < BX; ++x) pa[x] = A + low(i0 + 16 * x + li, M - 1) * K + (kbeg + kBase * lk);
     }
-    const T* pb = Bm + low(j0 + BY * li, N - BY) + (kbeg + E * lk) * N;
+    const T* pb = Bm + low(j0 + BY * li, N - BY) + (kbeg + kBase * lk) * N;
 
-    // FP64: the running sums; FP32: unused but by the repeat in FP32
+    // FP64: the running sums; else the 16-term sums of the FP32 instruction
     acc_t acc[BX][BY];
     double wide[kWide ? BX : 1][kWide ? BY : 1][4];
     auto clear = [&]() {
@@ -207,29 +230,45 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
         if constexpr (!TRANS_A) {
 #pragma unroll
             for (int x = 0; x < BX; ++x) {
-                T v[E];
-                load_vec<T, E>(pa[x] + k, v);
+                if constexpr (kStep == 1) {
+                    T v[E];
+                    load_vec<T, E>(pa[x] + k, v);
 #pragma unroll
-                for (int e = 0; e < E; ++e) f.a[e][x] = v[e];
+                    for (int e = 0; e < E; ++e) f.a[e][x] = v[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) f.a[e][x] = pa[x][k + kStep * e];
+                }
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < E; ++e) load_vec(pa[0] + (k + e) * M, f.a[e]);
+            for (int e = 0; e < E; ++e) load_vec(pa[0] + (k + kStep * e) * M, f.a[e]);
         }
 #pragma unroll
-        for (int e = 0; e < E; ++e) load_vec(pb + (k + e) * N, f.b[e]);
+        for (int e = 0; e < E; ++e) load_vec(pb + (k + kStep * e) * N, f.b[e]);
+    };
+    // FP32: the 16-term sums into the FP64 ones.
+    [[maybe_unused]] auto fold = [&]() {
+#pragma unroll
+        for (int x = 0; x < BX; ++x)
+#pragma unroll
+            for (int y = 0; y < BY; ++y) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)acc[x][y][r];
+                acc[x][y] = acc_t{0, 0, 0, 0};
+            }
     };
     // The products of one k-step; next() is called once f has been read.
     auto mma = [&](const F& f, auto next) {
-        if constexpr (!kWide) {
+        if constexpr (AR != SPLIT) {
 #pragma unroll
             for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int x = 0; x < BX; ++x)
 #pragma unroll
-                    for (int y = 0; y < BY; ++y)
-                        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[s][x], f.b[s][y], acc[x][y], 0, 0, 0);
+                    for (int y = 0; y < BY; ++y) acc[x][y] = MF::mac(f.a[s][x], f.b[s][y], acc[x][y]);
             next();
+            if constexpr (kWide) fold();
         } else {
             Split a[BX], b[BY];
 #pragma unroll
@@ -283,16 +322,17 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
             F z;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const bool in = t1 * KS + E * lk + e < K;
+                const int dk = kStep * e;
+                const bool in = t1 * KS + kBase * lk + dk < K;
 #pragma unroll
                 for (int x = 0; x < BX; ++x)
-                    z.a[e][x] = in ? (TRANS_A ? pa[0][(k0 + e) * M + x] : pa[TRANS_A ? 0 : x][k0 + e]) : T(0);
+                    z.a[e][x] = in ? (TRANS_A ? pa[0][(k0 + dk) * M + x] : pa[TRANS_A ? 0 : x][k0 + dk]) : T(0);
 #pragma unroll
-                for (int y = 0; y < BY; ++y) z.b[e][y] = in ? pb[(k0 + e) * N + y] : T(0);
+                for (int y = 0; y < BY; ++y) z.b[e][y] = in ? pb[(k0 + dk) * N + y] : T(0);
             }
             mma(z, [] {});
         }
-        if constexpr (kWide) {
+        if constexpr (AR == SPLIT) {
             // An operand or a sum that is not finite: the whole block again on
             // the FP32 instruction, whose infinities are those of the sums.
             bool bad = false;
@@ -323,16 +363,9 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
                         for (int x = 0; x < BX; ++x)
 #pragma unroll
                             for (int y = 0; y < BY; ++y)
-                                acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[x], bv[y], acc[x][y], 0, 0, 0);
+                                acc[x][y] = MF::mac(av[x], bv[y], acc[x][y]);
                     }
-#pragma unroll
-                    for (int x = 0; x < BX; ++x)
-#pragma unroll
-                        for (int y = 0; y < BY; ++y) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)acc[x][y][r];
-                            acc[x][y] = acc_t{0, 0, 0, 0};
-                        }
+                    fold();
                 }
             }
         }
@@ -412,17 +445,26 @@ using S5 = Shape<2, 1, 1, 1, 8, 3, 2, 2>;  // 32 x 16
 using S6 = Shape<1, 1, 1, 1, 8, 4, 2, 2>;  // 16 x 16, the one that takes any size
 struct ShapeInfo {
     int tm, tn, bx, by;
-    double cost[2];  // FP64, FP32
+    double cost[3];  // by Arith
 };
 template <typename S>
-constexpr ShapeInfo info(double c64, double c32) {
-    return {S::TM, S::TN, S::BX, S::BY, {c64, c32}};
+constexpr ShapeInfo info(double c64, double c32, double split) {
+    return {S::TM, S::TN, S::BX, S::BY, {c64, c32, split}};
 }
+
+// Whether FP32 operands are split.  Both forms round each product sum to some
+// 2^-24 of a term, differently; f, an FP64 result, averages that over its
+// entries (2e-7 / sqrt(m n) for the FP32 instruction, 1.2e-7 split).  Below
+// 2^20 entries, where the two could differ by 1e-9 of f and where latency hides
+// the slower instruction (1,024 x 1,024: 73 us against 60; 512 x 384: 19, 17),
+// f keeps the bits that the FP32 instruction's 16-term sums give it.
+bool splits(const BDenseView& b) { return b.dtype == F32 && b.m * b.n >= (1 << 20); }
+Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SPLIT : FP32; }
 // cost: picoseconds per product and entry of a tile with every compute unit
 // busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.
-constexpr ShapeInfo kShapes[] = {info<S0>(7.7, 4.3), info<S1>(7.8, 4.5),  info<S2>(9.1, 5.5),
-                                 info<S3>(9.1, 6.2), info<S4>(10.0, 6.6), info<S5>(16.0, 8.9),
-                                 info<S6>(22.7, 11.4)};
+constexpr ShapeInfo kShapes[] = {
+    info<S0>(7.7, 5.8, 4.3),   info<S1>(7.8, 5.8, 4.5),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.2),
+    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 8.9), info<S6>(22.7, 11.0, 11.4)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 int64_t tiles_of(const BDenseView& b, int sh) {
@@ -443,7 +485,7 @@ int bdense_shape(const BDenseView& b) {
     for (int i = 0; i < kNShapes; ++i) {
         const ShapeInfo& s = kShapes[i];
         if ((s.bx > 1 && b.m < 16 * s.bx) || (s.by > 1 && b.n < 16 * s.by)) continue;
-        const double t = (double)((tiles_of(b, i) + 255) / 256) * s.tm * s.tn * s.cost[b.dtype == F64 ? 0 : 1];
+        const double t = (double)((tiles_of(b, i) + 255) / 256) * s.tm * s.tn * s.cost[arith(b)];
         if (t < tbest) {
             tbest = t;
             best = i;
@@ -456,27 +498,29 @@ int64_t bdense_fwd_tiles(const BDenseView& b) { return tiles_of(b, b.shape); }
 
 namespace {
 
-template <typename T, bool TRANS, int EPI, typename S>
+template <typename T, int AR, bool TRANS, int EPI, typename S>
 hipError_t launch_shape(const BDenseView& b, hipStream_t s, const T* A, const T* Bm, const T* W,
-                        double* partials, T* V, const double* fbar, T* G, int accumulate) {
+                        double* partials, T* V, const double* fbar, T* G, int accumulate, int64_t np,
+                        double* f_out) {
     const int64_t tn = (b.n + S::TN - 1) / S::TN, nt = tn * ((b.m + S::TM - 1) / S::TM);
     if (nt > 0x7fffffffLL) return hipErrorInvalidValue;
-    PG_LAUNCH((k_gemm_mfma<T, TRANS, EPI, S>), dim3((unsigned)nt), dim3(S::NTHR), 0, s, A, Bm, b.m,
-              b.n, b.m, W, partials, V, fbar, G, accumulate, (int)tn);
+    PG_LAUNCH((k_gemm_mfma<T, AR, TRANS, EPI, S>), dim3((unsigned)nt + (f_out ? 1 : 0)), dim3(S::NTHR), 0,
+              s, A, Bm, b.m, b.n, b.m, W, partials, V, fbar, G, accumulate, (int)tn, np, f_out);
     return hipGetLastError();
 }
 
-template <typename T, bool TRANS, int EPI>
+template <typename T, int AR, bool TRANS, int EPI>
 hipError_t launch_gemm(const BDenseView& b, hipStream_t s, const T* A, const T* Bm, const T* W,
-                       double* partials, T* V, const double* fbar, T* G, int accumulate) {
+                       double* partials, T* V, const double* fbar, T* G, int accumulate, int64_t np,
+                       double* f_out) {
     switch (b.shape) {
-        case 0: return launch_shape<T, TRANS, EPI, S0>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 1: return launch_shape<T, TRANS, EPI, S1>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 2: return launch_shape<T, TRANS, EPI, S2>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 3: return launch_shape<T, TRANS, EPI, S3>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 4: return launch_shape<T, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 5: return launch_shape<T, TRANS, EPI, S5>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
-        case 6: return launch_shape<T, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate);
+        case 0: return launch_shape<T, AR, TRANS, EPI, S0>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 1: return launch_shape<T, AR, TRANS, EPI, S1>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 2: return launch_shape<T, AR, TRANS, EPI, S2>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 3: return launch_shape<T, AR, TRANS, EPI, S3>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 4: return launch_shape<T, AR, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 5: return launch_shape<T, AR, TRANS, EPI, S5>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 6: return launch_shape<T, AR, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
     }
     return hipErrorInvalidValue;
 }
@@ -487,22 +531,32 @@ hipError_t launch_bdense_fwd(const BDenseView& b, const void* X, double* partial
                              hipStream_t s) {
     if (b.m == 0 || b.n == 0) return hipSuccess;
     if (b.dtype == F64)
-        return launch_gemm<double, false, EPI_FWD>(b, s, (const double*)b.A, (const double*)X,
+        return launch_gemm<double, FP64, false, EPI_FWD>(b, s, (const double*)b.A, (const double*)X,
                                                    (const double*)b.W, partials, (double*)V, nullptr,
-                                                   nullptr, 0);
-    return launch_gemm<float, false, EPI_FWD>(b, s, (const float*)b.A, (const float*)X,
-                                              (const float*)b.W, partials, (float*)V, nullptr,
-                                              nullptr, 0);
+                                                   nullptr, 0, 0, nullptr);
+    const float *A = (const float*)b.A, *Xp = (const float*)X, *W = (const float*)b.W;
+    if (splits(b))
+        return launch_gemm<float, SPLIT, false, EPI_FWD>(b, s, A, Xp, W, partials, (float*)V, nullptr,
+                                                         nullptr, 0, 0, nullptr);
+    return launch_gemm<float, FP32, false, EPI_FWD>(b, s, A, Xp, W, partials, (float*)V, nullptr,
+                                                    nullptr, 0, 0, nullptr);
 }
 
 hipError_t launch_bdense_bwd(const BDenseView& b, const void* V, const double* fbar, void* G,
-                             int accumulate, hipStream_t s) {
-    if (b.m == 0 || b.n == 0) return hipSuccess;
+                             int accumulate, const double* partials, int64_t np, double* f_out,
+                             hipStream_t s) {
+    if (b.m == 0 || b.n == 0)
+        return f_out ? launch_final_sum(partials, np, f_out, s) : hipSuccess;
+    double* part = const_cast<double*>(partials);  // read only in the backward product
     if (b.dtype == F64)
-        return launch_gemm<double, true, EPI_BWD>(b, s, (const double*)b.A, (const double*)V, nullptr,
-                                                  nullptr, nullptr, fbar, (double*)G, accumulate);
-    return launch_gemm<float, true, EPI_BWD>(b, s, (const float*)b.A, (const float*)V, nullptr,
-                                             nullptr, nullptr, fbar, (float*)G, accumulate);
+        return launch_gemm<double, FP64, true, EPI_BWD>(b, s, (const double*)b.A, (const double*)V, nullptr,
+                                                  part, nullptr, fbar, (double*)G, accumulate, np, f_out);
+    const float *A = (const float*)b.A, *Vp = (const float*)V;
+    if (splits(b))
+        return launch_gemm<float, SPLIT, true, EPI_BWD>(b, s, A, Vp, nullptr, part, nullptr, fbar,
+                                                        (float*)G, accumulate, np, f_out);
+    return launch_gemm<float, FP32, true, EPI_BWD>(b, s, A, Vp, nullptr, part, nullptr, fbar,
+                                                   (float*)G, accumulate, np, f_out);
 }
 
 }  // namespace pg

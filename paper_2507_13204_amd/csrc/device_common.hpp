@@ -85,6 +85,65 @@ __device__ __forceinline__ void atomic_add_f64(double* p, double v) {
     unsafeAtomicAdd(p, v);
 }
 
+// Handing values to whichever workgroup finishes last, without device-scope
+// fences.  A release fence writes back the whole L2 and an acquire fence
+// invalidates it, some microseconds on a launch of a few; nothing else in
+// those caches has to be seen.  So the values themselves go through the
+// coherence point: a value is stored by an agent-scope atomic store (or added
+// by an agent-scope atomic), the storing wave waits until its memory
+// operations are performed (publish_wait), and only then is the ticket taken;
+// the workgroup that finds itself last reads the values with agent-scope
+// atomic loads, which never return a line an XCD's own cache still holds.
+// Where several waves publish, each waits for its own before the workgroup
+// barrier that precedes the ticket.
+__device__ __forceinline__ void publish(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_wait() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the compiler keeps the order too
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+__device__ __forceinline__ double read_published(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Sum of p[0 .. n) by a workgroup of any size (whole waves), valid in thread
+// 0, with the same bits whatever the size: as 1,024 threads would, entry t,
+// t + 1024, ... to thread t, a butterfly per 64 of them, a butterfly over
+// those 16.  lds holds 16 doubles.  PUB: the entries were published.
+template <bool PUB>
+__device__ __forceinline__ double final_sum_block(const double* __restrict__ p, int64_t n, double* lds) {
+    constexpr int kU = 8, kVW = 16, kStride = kVW * kWave;  // loads in flight; virtual waves
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    for (int vw = wid; vw < kVW; vw += nw) {
+        double s = 0.0;
+        for (int64_t q = vw * kWave + lane; q < n; q += kU * kStride) {
+            double v[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int64_t i = q + u * kStride;
+                v[u] = i < n ? (PUB ? __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                    : p[i])
+                             : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+                if (q + u * kStride < n) s += v[u];
+        }
+        s = wave_sum(s);
+        if (lane == 0) lds[vw] = s;
+    }
+    __syncthreads();
+    double r = 0.0;
+    if (wid == 0) r = wave_sum(lane < kVW ? lds[lane] : 0.0);
+    return r;
+}
+
+// Takes the ticket; true for the last of n.
+__device__ __forceinline__ bool take_ticket(int32_t* ticket, int n) {
+    return __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+}
+
 template <typename T>
 __device__ __forceinline__ double to_f64(T v) {
     return static_cast<double>(v);

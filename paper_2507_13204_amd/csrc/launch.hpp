@@ -96,7 +96,17 @@ struct MeshPass {
     int combine = 1;               // combine atomic contributions in LDS first
     uint32_t hash_shift = kHashRotDefault;  // LDS table hash parameter (see agg_slot)
     int agg_slots = 4096;          // LDS table size: 4096 or 2048 (see choose_hash_shift)
+    // With a ticket (zero between launches, re-armed by the launch) the last
+    // workgroup sums the partials into f_out; partial_base is then 0.
+    int32_t* ticket = nullptr;
+    double* f_out = nullptr;
 };
+// Grids up to which the last workgroup sums f: each workgroup waits for its
+// two trips to the coherence point while it holds its place on the compute
+// unit, which costs more than a launch where there are more than fit at once.
+// FP64 gradients (launch / ticket, us): 35 workgroups 11.6 / 9.1, 116 11.2 /
+// 10.1, 203 10.8 / 11.0, 325 12.4 / 13.5, 963 19.4 / 26.1.
+constexpr int64_t kTicketBlocks = 160;
 
 // Number of workgroups an element pass over n items launches.
 int64_t mesh_blocks(int64_t n_items, int block, int ept);
@@ -158,16 +168,20 @@ size_t tiled_lds_bytes(int tile, int32_t k);
 // Level 1 (obj: with the objective partial per tile into p.partials) and level 2.
 hipError_t launch_mesh_tiled(const MeshView& m, const MeshPass& p, const TiledView& tv, bool obj,
                              hipStream_t s);
+// Level 2 also writes f (when f_out is not null): the sum of partials[0 .. np)
+// with k_final_sum's bits.
 hipError_t launch_node_tiled(const MeshView& m, const TiledView& tv, void* grad, int accumulate,
-                             hipStream_t s);
+                             const double* partials, int64_t np, double* f_out, hipStream_t s);
 
 hipError_t launch_mesh_elem(const MeshView& m, MeshMode mode, const MeshPass& p, hipStream_t s);
 
 // Node-parallel gather of the reverse pass over the transposed connectivity:
-// g[n] (+)= sum_{p in offs[n]..offs[n+1]} v[inc[p]/k] * B[inc[p]].
+// g[n] (+)= sum_{p in offs[n]..offs[n+1]} v[inc[p]/k] * B[inc[p]]; f as in
+// launch_node_tiled.
 hipError_t launch_mesh_node_gather(const MeshView& m, const int32_t* offs, const int32_t* inc,
                                    const void* binc, const double* v, void* grad, int accumulate,
-                                   int block, hipStream_t s);
+                                   int block, const double* partials, int64_t np, double* f_out,
+                                   hipStream_t s);
 
 // out[0] (=|+=) sum of partials[0..n) in a fixed order (one workgroup).
 hipError_t launch_final_sum(const double* partials, int64_t n, double* out, hipStream_t s);
@@ -325,9 +339,11 @@ int bdense_shape(const BDenseView& b);
 int64_t bdense_fwd_tiles(const BDenseView& b);
 hipError_t launch_bdense_fwd(const BDenseView& b, const void* X, double* partials, void* V,
                              hipStream_t s);
-// Backward: G (=|+=) fbar * A^T V.
+// Backward: G (=|+=) fbar * A^T V; when f_out is not null a workgroup more
+// writes f, the sum of partials[0 .. np) with k_final_sum's bits.
 hipError_t launch_bdense_bwd(const BDenseView& b, const void* V, const double* fbar, void* G,
-                             int accumulate, hipStream_t s);
+                             int accumulate, const double* partials, int64_t np, double* f_out,
+                             hipStream_t s);
 
 }  // namespace pg
 

@@ -22,6 +22,25 @@ namespace pg {
 
 namespace {
 
+// The workgroup's partial of f handed over, and summed by the last of the
+// grid's workgroups, in the order of a launch of its own.
+__device__ __forceinline__ void sum_by_ticket(const MeshPass& p, uint32_t lb, double s, double* lds) {
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        publish(p.partials + lb, s);
+        publish_wait();
+        last = take_ticket(p.ticket, (int)gridDim.x);
+    }
+    __syncthreads();
+    if (last) {
+        const double f = final_sum_block<true>(p.partials, gridDim.x, lds);
+        if (threadIdx.x == 0) {
+            p.f_out[0] = f;
+            *p.ticket = 0;
+        }
+    }
+}
+
 // Compile-time K: every row lives in registers.
 template <typename T, int K, int MODE, int EPT, int AGG>
 __global__ void __launch_bounds__(1024)
@@ -43,7 +62,10 @@ k_mesh_elem(MeshView m, MeshPass p) {
         a, (int64_t)lb * blockDim.x * EPT, n_items, 0, fb, tab);
     if constexpr (has_sum(MODE)) {
         const double s = block_sum_dyn(tsum, lds);
-        if (threadIdx.x == 0) p.partials[p.partial_base + lb] = s;
+        if (p.ticket)
+            sum_by_ticket(p, lb, s, lds);
+        else if (threadIdx.x == 0)
+            p.partials[p.partial_base + lb] = s;
     }
 }
 
@@ -65,7 +87,10 @@ k_mesh_elem_any(MeshView m, MeshPass p) {
         elem_any<T, KM, MODE, AGG>(a, m.k, (int64_t)lb * blockDim.x, n_items, 0, fb, tab);
     if constexpr (has_sum(MODE)) {
         const double s = block_sum_dyn(tsum, lds);
-        if (threadIdx.x == 0) p.partials[p.partial_base + lb] = s;
+        if (p.ticket)
+            sum_by_ticket(p, lb, s, lds);
+        else if (threadIdx.x == 0)
+            p.partials[p.partial_base + lb] = s;
     }
 }
 
@@ -120,7 +145,10 @@ k_mesh_elem_dyn(MeshView m, MeshPass p) {
     }
     if constexpr (has_sum(MODE)) {
         const double s = block_sum_dyn(tsum, lds);
-        if (threadIdx.x == 0) p.partials[p.partial_base + lb] = s;
+        if (p.ticket)
+            sum_by_ticket(p, lb, s, lds);
+        else if (threadIdx.x == 0)
+            p.partials[p.partial_base + lb] = s;
     }
 }
 
@@ -133,8 +161,17 @@ template <typename T, int K>
 __global__ void __launch_bounds__(1024)
 k_mesh_node_gather(int64_t n_nodes, int32_t k, const int32_t* __restrict__ offs,
                    const int32_t* __restrict__ inc, const double* __restrict__ v,
-                   const T* __restrict__ binc, T* __restrict__ grad, int accumulate) {
-    const uint32_t lb = xcd_remap(blockIdx.x, gridDim.x);
+                   const T* __restrict__ binc, T* __restrict__ grad, int accumulate,
+                   const double* __restrict__ partials, int64_t np, double* __restrict__ f_out) {
+    // One workgroup more than the nodes need sums f (one launch fewer).
+    const uint32_t nb = gridDim.x - (f_out ? 1 : 0);
+    if (blockIdx.x == nb) {
+        __shared__ double lds[16];
+        const double f = final_sum_block<false>(partials, np, lds);
+        if (threadIdx.x == 0) f_out[0] = f;
+        return;
+    }
+    const uint32_t lb = xcd_remap(blockIdx.x, nb);
     const int64_t n = (int64_t)lb * blockDim.x + threadIdx.x;
     if (n >= n_nodes) return;
     const int32_t p0 = offs[n], p1 = offs[n + 1];
@@ -271,27 +308,28 @@ hipError_t launch_mesh_elem(const MeshView& m, MeshMode mode, const MeshPass& p,
 
 hipError_t launch_mesh_node_gather(const MeshView& m, const int32_t* offs, const int32_t* inc,
                                    const void* binc, const double* v, void* grad, int accumulate,
-                                   int block, hipStream_t s) {
-    if (m.n_nodes == 0) return hipSuccess;
-    const unsigned nb = (unsigned)((m.n_nodes + block - 1) / block);
+                                   int block, const double* partials, int64_t np, double* f_out,
+                                   hipStream_t s) {
+    if (m.n_nodes == 0 && !f_out) return hipSuccess;
+    const unsigned nb = (unsigned)((m.n_nodes + block - 1) / block) + (f_out ? 1 : 0);
     if (m.dtype == F64) {
         if (m.k == 8)
             hipLaunchKernelGGL((k_mesh_node_gather<double, 8>), dim3(nb), dim3(block), 0, s,
                                m.n_nodes, m.k, offs, inc, v, (const double*)binc, (double*)grad,
-                               accumulate);
+                               accumulate, partials, np, f_out);
         else
             hipLaunchKernelGGL((k_mesh_node_gather<double, 0>), dim3(nb), dim3(block), 0, s,
                                m.n_nodes, m.k, offs, inc, v, (const double*)binc, (double*)grad,
-                               accumulate);
+                               accumulate, partials, np, f_out);
     } else {
         if (m.k == 8)
             hipLaunchKernelGGL((k_mesh_node_gather<float, 8>), dim3(nb), dim3(block), 0, s,
                                m.n_nodes, m.k, offs, inc, v, (const float*)binc, (float*)grad,
-                               accumulate);
+                               accumulate, partials, np, f_out);
         else
             hipLaunchKernelGGL((k_mesh_node_gather<float, 0>), dim3(nb), dim3(block), 0, s,
                                m.n_nodes, m.k, offs, inc, v, (const float*)binc, (float*)grad,
-                               accumulate);
+                               accumulate, partials, np, f_out);
     }
     return hipGetLastError();
 }

@@ -368,14 +368,13 @@ __device__ __forceinline__ void store_products(const GroupDev& g, int64_t i, con
 template <int BS>
 __device__ __forceinline__ void sum_by_last(const GroupDev& g, double* lds, int* last_wg) {
     if (threadIdx.x == 0) {
-        __threadfence();  // this workgroup's partial before its ticket
-        *last_wg = atomicAdd(g.ticket, 1) == (int)gridDim.x - 1;
+        publish_wait();  // its partial
+        *last_wg = take_ticket(g.ticket, (int)gridDim.x);
     }
     __syncthreads();
     if (*last_wg) {
-        __threadfence();  // every partial is visible
         double v = 0.0;
-        for (int q = threadIdx.x; q < (int)gridDim.x; q += BS) v += g.partials[q];
+        for (int q = threadIdx.x; q < (int)gridDim.x; q += BS) v += read_published(g.partials + q);
         v = block_sum<BS>(v, lds);
         if (threadIdx.x == 0) {
             *g.f_out = v;
@@ -475,7 +474,7 @@ __global__ void __launch_bounds__(kBS) k_group_lds(GroupDev g) {
     if constexpr (FWD) {
         if (g.sum_slot >= 0) {
             const double t = block_sum<kBS>(ok ? r[g.sum_slot * kBS] : 0.0, lds);
-            if (tid == 0) g.partials[blockIdx.x] = t;
+            if (tid == 0) publish(g.partials + blockIdx.x, t);
         }
     }
     if constexpr (REV) {
@@ -591,7 +590,7 @@ __global__ void __launch_bounds__(BS) k_group(GroupDev g) {
     if constexpr (FWD) {
         if (g.sum_slot >= 0) {
             const double t = block_sum<BS>(ok ? r.get(g.sum_slot) : 0.0, lds);
-            if (threadIdx.x == 0) g.partials[blockIdx.x] = t;
+            if (threadIdx.x == 0) publish(g.partials + blockIdx.x, t);
         }
     }
     if constexpr (REV) {

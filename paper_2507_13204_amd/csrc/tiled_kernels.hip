@@ -217,8 +217,17 @@ k_mesh_tiled_rounds(MeshView m, MeshPass p, TiledView tv) {
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_node_tiled(int64_t n_nodes, const int32_t* __restrict__ noff, const int32_t* __restrict__ npos,
-             const double* __restrict__ stage, T* __restrict__ grad, int accumulate) {
-    const int64_t n = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+             const double* __restrict__ stage, T* __restrict__ grad, int accumulate,
+             const double* __restrict__ partials, int64_t np, double* __restrict__ f_out) {
+    // One workgroup more than the nodes need sums f (one launch fewer).
+    const unsigned nb = gridDim.x - (f_out ? 1 : 0);
+    if (blockIdx.x == nb) {
+        __shared__ double lds[16];
+        const double f = final_sum_block<false>(partials, np, lds);
+        if (threadIdx.x == 0) f_out[0] = f;
+        return;
+    }
+    const int64_t n = (int64_t)xcd_remap(blockIdx.x, nb) * blockDim.x + threadIdx.x;
     if (n >= n_nodes) return;
     const int32_t q0 = noff[n], q1 = noff[n + 1];
     double s = 0.0;
@@ -289,15 +298,15 @@ hipError_t launch_mesh_tiled(const MeshView& m, const MeshPass& p, const TiledVi
 }
 
 hipError_t launch_node_tiled(const MeshView& m, const TiledView& tv, void* grad, int accumulate,
-                             hipStream_t s) {
-    if (m.n_nodes == 0) return hipSuccess;
-    const dim3 grid((unsigned)((m.n_nodes + 255) / 256)), block(256);
+                             const double* partials, int64_t np, double* f_out, hipStream_t s) {
+    if (m.n_nodes == 0 && !f_out) return hipSuccess;
+    const dim3 grid((unsigned)((m.n_nodes + 255) / 256) + (f_out ? 1 : 0)), block(256);
     if (m.dtype == F64)
         hipLaunchKernelGGL(k_node_tiled<double>, grid, block, 0, s, m.n_nodes, tv.noff, tv.npos, tv.stage,
-                           (double*)grad, accumulate);
+                           (double*)grad, accumulate, partials, np, f_out);
     else
         hipLaunchKernelGGL(k_node_tiled<float>, grid, block, 0, s, m.n_nodes, tv.noff, tv.npos, tv.stage,
-                           (float*)grad, accumulate);
+                           (float*)grad, accumulate, partials, np, f_out);
     return hipGetLastError();
 }
 

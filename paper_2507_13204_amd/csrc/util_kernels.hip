@@ -32,7 +32,7 @@ __device__ __forceinline__ double strided_sum(const double* __restrict__ p, int6
 __global__ void __launch_bounds__(1024)
 k_final_sum(const double* __restrict__ partials, int64_t n, double* __restrict__ out) {
     __shared__ double lds[16];
-    const double s = block_sum_dyn(strided_sum(partials, 0, n), lds);
+    const double s = final_sum_block<false>(partials, n, lds);
     if (threadIdx.x == 0) out[0] = s;
 }
 
