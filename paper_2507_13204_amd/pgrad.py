@@ -5,7 +5,8 @@ name through :func:`lib`; the classes below own a plan and its workspace and
 pass torch tensors' device pointers and the current HIP stream.  All the
 arithmetic happens in the library's HIP kernels: if the library is missing
 or cannot be loaded, every call raises :class:`PgError` -- there is no
-fallback path.
+fallback path.  The autograd Functions take plain tensors through a native
+node (_pgrad_torch.so, the same library calls), others through Python.
 """
 from __future__ import annotations
 
@@ -807,7 +808,18 @@ class _ObjectiveFn(torch.autograd.Function):
 
     @classmethod
     def apply(cls, x, obj):
-        return super().apply(x, obj, bool(torch.is_grad_enabled() and x.requires_grad))
+        want_grad = bool(torch.is_grad_enabled() and x.requires_grad)
+        if want_grad and type(x) in _PLAIN_TENSORS and type(obj) in _NODE_OBJECTIVES \
+                and cls in _NODE_LABELS:
+            policy = _NODE_POLICIES.get(obj.autograd_policy)
+            if policy is not None:
+                batch = type(obj) is MeshBatch
+                tape = (obj.tape_bytes() + 15) // 16 * 2 if policy else 0
+                f = _node().apply(x, obj, obj._plan.value or 0, policy, obj.n_inst if batch else -1,
+                                  tape, _NODE_LABELS[cls], check)
+                if f is not None:
+                    return f
+        return super().apply(x, obj, want_grad)
 
     @staticmethod
     def forward(ctx, x, obj, want_grad):
@@ -871,6 +883,29 @@ class MeshBatchFn(_ObjectiveFn):
     """Per-instance objectives of a MeshBatch (a vector output): the policy
     keeps u_e on a per-call tape or nothing; the backward seeds each
     instance with its own grad_output entry."""
+
+
+# What the native node takes: these classes themselves (a subclass may change
+# what a forward does) with plain tensors.
+_PLAIN_TENSORS = (torch.Tensor, torch.nn.Parameter)
+_NODE_OBJECTIVES = (MeshObjective, DenseObjective, BatchedDense, MeshBatch)
+_NODE_POLICIES = {"gradient": 0, "store": 1}
+_NODE_LABELS = {c: c.__name__ + "Backward" for c in (MeshFn, DenseFn, BatchedDenseFn, MeshBatchFn)}
+_node_module = None
+
+
+def _node():
+    """_pgrad_torch.so (built with libpgrad.so); raise if absent."""
+    global _node_module
+    if _node_module is None:
+        lib()
+        try:
+            from . import _pgrad_torch
+        except ImportError as e:
+            raise PgError(EHIP, "load", f"_pgrad_torch.so: {e} (build it with "
+                          "`python -m paper_2507_13204_amd.build`)") from e
+        _node_module = _pgrad_torch
+    return _node_module
 
 
 class ProgramFn(torch.autograd.Function):
