@@ -466,13 +466,15 @@ struct GroupDev {
 };
 
 // The reverse of a gather of n_elems rows of k entries (conn, coefficients B)
-// whose products lie in the order of the transposed connectivity: out[n]
-// (=|+=) sum of prod[offs[n] .. offs[n + 1]).  While *stale is 0; else conn is
+// whose products lie in the order of the transposed connectivity, in 1 or kXcds
+// parts: out[n] (=|+=) sum over the parts c of prod[offs[m] .. offs[m + 1]), m =
+// c n_nodes + n.  While *stale is 0; else conn is
 // no longer what that order was computed from, and B adj is scattered by
 // element with atomics.
+constexpr int kXcds = 8;  // as xcd_remap
 struct GatherRev {
     int64_t n_nodes = 0, n_elems = 0;
-    int32_t k = 0;
+    int32_t k = 0, parts = 1;
     const int32_t* offs = nullptr;
     const double* prod = nullptr;
     const int32_t* conn = nullptr;
@@ -483,6 +485,10 @@ struct GatherRev {
     int accumulate = 1;
 };
 hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s);
+// Per incidence, part * n_nodes + entry: the part is the XCD that a group's
+// launch handles the row on.
+hipError_t launch_part_keys(const int32_t* conn, int64_t n_elems, int32_t k, int64_t n_nodes,
+                            int32_t* keys, hipStream_t s);
 
 enum GroupMode { G_FWD = 0, G_REV = 1, G_FWDREV = 2 };
 

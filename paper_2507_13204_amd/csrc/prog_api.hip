@@ -82,6 +82,7 @@ struct Group {
     // (decided at bind from the connectivity).
     size_t pos_off = NONE, offs_off = NONE, cursor_off = NONE, copy_off = NONE, adj_off = NONE,
            prod_off = NONE, csr_scan_off = NONE;
+    int32_t parts = 1;          // parts of the products' order (GatherRev)
     bool gather_first = false;  // its delivery is the first into the operand's shadow
     bool transposed = false;
 };
@@ -126,6 +127,14 @@ namespace {
 // to which the plan keeps room for it (16 bytes and a share per incidence:
 // some 150 MB).
 constexpr int64_t kTransposeMin = 1 << 16, kTransposeMax = 1 << 23;
+// The products are kept in one part per XCD up to this many bytes of operand
+// and of one XCD's products, where its L2 (4 MB) holds most of both; beyond, the
+// offsets of the parts cost more than the merged stores save.  Group and pass in
+// parts against one list, us: 2.4 MB (rows of eight on 100,000 entries) 33.4 and
+// 42.4, 4.0 MB (300,007) 35.6 and 42.9, 6.0 MB (500,000) 49.4 and 51.6, 6.4 MB
+// (400,000) 80.5 and 79.6, 12 MB (10^6) 143 and 117.  And only with at most one
+// operand entry per incidence: the offsets then take no more than the products.
+constexpr int64_t kPartBytes = 6 << 20;
 // Incidences of one operand entry up to which one thread adds them.
 constexpr int32_t kTransposeDegree = 256;
 
@@ -650,10 +659,12 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
         g.pos_off = take(sizeof(int32_t) * (size_t)inc);
         g.prod_off = take(sizeof(double) * (size_t)inc);
         g.copy_off = take(sizeof(int32_t) * (size_t)inc);
-        g.offs_off = take(sizeof(int32_t) * (size_t)(nn + 1));
-        g.cursor_off = take(sizeof(int32_t) * (size_t)nn);
+        g.parts = nn <= inc && 8 * nn + inc <= kPartBytes ? kXcds : 1;
+        const int64_t runs = nn * g.parts;
+        g.offs_off = take(sizeof(int32_t) * (size_t)(runs + 1));
+        g.cursor_off = take(sizeof(int32_t) * (size_t)runs);
         g.adj_off = take(sizeof(double) * (size_t)op.n);
-        g.csr_scan_off = take(sizeof(int64_t) * (size_t)scan_scratch_items(nn));
+        g.csr_scan_off = take(sizeof(int64_t) * (size_t)scan_scratch_items(runs));
     }
     p->ws_bytes = off;
 
@@ -767,12 +778,20 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
             int32_t degree = 0;
             PG_HIP(hipMemcpy(&degree, flag + 2, sizeof degree, hipMemcpyDeviceToHost));
             if (degree <= kTransposeDegree) {
-                PG_HIP(launch_exclusive_scan(cursor, nn, offs, reinterpret_cast<int64_t*>(w + g.csr_scan_off),
-                                             nullptr));
                 // the incidence list is needed only for its inverse: it is
-                // built where the products will be
+                // built where the products will be, as are its keys
                 int32_t* list = reinterpret_cast<int32_t*>(w + g.prod_off);
-                PG_HIP(launch_csr_fill_sort(copy, inc, nn, offs, cursor, list, nullptr));
+                int32_t* keys = copy;
+                const int64_t runs = nn * g.parts;
+                if (g.parts > 1) {
+                    keys = list + inc;
+                    PG_HIP(launch_part_keys(copy, op.n, op.k, nn, keys, nullptr));
+                    PG_HIP(launch_zero(cursor, sizeof(int32_t) * (size_t)runs, nullptr));
+                    PG_HIP(launch_validate_count(keys, inc, runs, cursor, flag, nullptr));
+                }
+                PG_HIP(launch_exclusive_scan(cursor, runs, offs,
+                                             reinterpret_cast<int64_t*>(w + g.csr_scan_off), nullptr));
+                PG_HIP(launch_csr_fill_sort(keys, inc, runs, offs, cursor, list, nullptr));
                 PG_HIP(launch_invert(list, inc, reinterpret_cast<int32_t*>(w + g.pos_off), nullptr));
                 g.transposed = true;
                 if (g.gather_first) p->stored_first[(size_t)op.a] = 1;
@@ -939,6 +958,7 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
         r.n_nodes = ops[(size_t)go.a].n;
         r.n_elems = go.n;
         r.k = go.k;
+        r.parts = g.parts;
         r.offs = reinterpret_cast<const int32_t*>(p->ws + g.offs_off);
         r.prod = at(p, g.prod_off);
         r.conn = go.conn;

@@ -58,32 +58,71 @@ k_r_stencil(int64_t n, const double* __restrict__ yb, ProgTaps taps, double* __r
 }
 
 // The reverse of a gather whose products lie in the order of its transposed
-// connectivity: entry n adds its run of them, in ascending incidence order,
-// and stores the sum (or adds it to what is there).  Streams the products; a
-// stale plan only clears here what k_gather_scatter then adds to.  Random
-// rows of eight, 200,003 of them on 300,007 entries (1.6 M incidences): one
-// atomic per incidence bound the group at 121 us (13 G/s); the products'
-// stores and this pass take 28, against 35 for a pass that reads B and the
-// adjoint through the incidence list (500,000 rows on 10^6: 66 against 116).
+// connectivity, in C parts: entry n adds its run of each part, in ascending
+// incidence order over all of them, and stores the sum (or adds it to what is
+// there).  Streams the products, the first D of every run read ahead; a stale
+// plan only clears here what k_gather_scatter then adds to.
+//
+// With C = kXcds the part is the XCD whose workgroups store the products
+// (xcd_remap): in one list each 128-byte line collected its 16 products
+// through several L2s, which write the line back in pieces.  Random rows of
+// eight, 200,003 of them on 300,007 entries (1.6 M incidences), the group and
+// this pass: 121 us with one atomic per incidence (13 G/s), 42.9 in one list,
+// 35.6 in parts.  (Reading B and the adjoint through the incidence list
+// instead of storing products: 7 us more than one list.)
+template <int C>
 __global__ void __launch_bounds__(kBS) k_gather_rev(GatherRev r) {
-    constexpr int D = 8;
+    constexpr int D = C == 1 ? 8 : 4;
     const int64_t n = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kBS + threadIdx.x;
     if (n >= r.n_nodes) return;
     if (*r.stale) {
         if (!r.accumulate) r.out[n] = 0.0;
         return;
     }
-    const int32_t p0 = r.offs[n], p1 = r.offs[n + 1];
-    double s = 0.0;
-    for (int32_t p = p0; p < p1; p += D) {
-        double v[D];
+    int32_t p0[C], p1[C];
 #pragma unroll
-        for (int q = 0; q < D; ++q) v[q] = p + q < p1 ? r.prod[p + q] : 0.0;
+    for (int c = 0; c < C; ++c) {
+        p0[c] = r.offs[c * r.n_nodes + n];
+        p1[c] = r.offs[c * r.n_nodes + n + 1];
+    }
+    double v[C][D];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+#pragma unroll
+        for (int q = 0; q < D; ++q) v[c][q] = p0[c] + q < p1[c] ? r.prod[p0[c] + q] : 0.0;
+    }
+    const double was = r.accumulate ? r.out[n] : 0.0;
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
 #pragma unroll
         for (int q = 0; q < D; ++q)
-            if (p + q < p1) s += v[q];
+            if (p0[c] + q < p1[c]) s += v[c][q];
+        for (int32_t p = p0[c] + D; p < p1[c]; p += D) {
+            double w[D];
+#pragma unroll
+            for (int q = 0; q < D; ++q) w[q] = p + q < p1[c] ? r.prod[p + q] : 0.0;
+#pragma unroll
+            for (int q = 0; q < D; ++q)
+                if (p + q < p1[c]) s += w[q];
+        }
     }
-    r.out[n] = r.accumulate ? r.out[n] + s : s;
+    r.out[n] = r.accumulate ? was + s : s;
+}
+
+// Of each incidence of n_elems rows of k: its entry, and in which part of the
+// products the workgroup that handles its row stores (key = part * n_nodes +
+// entry).
+__global__ void __launch_bounds__(kBS)
+k_part_keys(const int32_t* __restrict__ conn, int64_t n_elems, int32_t k, int64_t n_nodes,
+            int32_t* __restrict__ keys) {
+    const int64_t blocks = (n_elems + kBS - 1) / kBS, q = blocks / kXcds, r = blocks % kXcds;
+    for (int64_t i = (int64_t)blockIdx.x * kBS + threadIdx.x; i < n_elems * k;
+         i += (int64_t)gridDim.x * kBS) {
+        const int64_t b = i / k / kBS;  // parts 0 .. r - 1 have q + 1 workgroups, the rest q
+        const int64_t part = b < r * (q + 1) ? b / (q + 1) : r + (b - r * (q + 1)) / q;
+        keys[i] = (int32_t)(part * n_nodes + conn[i]);
+    }
 }
 
 // The same by element with atomics, for a connectivity changed since the
@@ -748,10 +787,23 @@ hipError_t launch_group(const GroupDev& g, int mode, hipStream_t s) {
     return launch_group_ns<-1>(g, mode, s);
 }
 
+hipError_t launch_part_keys(const int32_t* conn, int64_t n_elems, int32_t k, int64_t n_nodes,
+                            int32_t* keys, hipStream_t s) {
+    if (n_elems == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_part_keys, dim3(std::min(nblocks(n_elems * k), 8192u)), dim3(kBS), 0, s, conn,
+                       n_elems, k, n_nodes, keys);
+    return hipGetLastError();
+}
+
 hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s) {
     if (r.n_nodes == 0) return hipSuccess;
     const dim3 grid(nblocks(r.n_nodes)), block(kBS);
-    PG_LAUNCH(k_gather_rev, grid, block, 0, s, r);
+    if (r.parts == 1)
+        PG_LAUNCH(k_gather_rev<1>, grid, block, 0, s, r);
+    else if (r.parts == kXcds)
+        PG_LAUNCH(k_gather_rev<kXcds>, grid, block, 0, s, r);
+    else
+        return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_gather_scatter, dim3(std::min(nblocks(r.n_elems), 256u)), block, 0, s, r);
     return hipGetLastError();
 }

@@ -97,3 +97,21 @@ def test_changed_connectivity_and_coefficients(k, twice, fusion):
         f, (g,) = prog.run([to_dev(x)])
         f_ref, (g_ref,) = OP.gradient(_spec(n, cd.cpu().numpy(), Bd.cpu().numpy(), w, twice), [x])
         assert srel(f.item(), f_ref) < TOL_F64_F and rel(g.cpu().numpy(), g_ref) < TOL_F64_G, step
+
+
+@pytest.mark.parametrize("n,E,k", [
+    (700_001, 100_003, 8),  # one list: operand and products past the caches
+    (300_007, 30_011, 8),   # one list: fewer incidences than entries
+    (66_001, 8_300, 8),     # a part per XCD, 33 workgroups: one part longer
+    (30_011, 210_000, 5),   # some 35 incidences per entry: runs past the first reads
+])
+def test_parts_of_the_products(n, E, k):
+    """The products in one list and in one part per XCD (the same fixed order)."""
+    x, conn, B, w = _case(n, E, k, 33)
+    spec = _spec(n, conn, B, w)
+    prog, (f, (g,)) = _run(spec, x, 1)
+    assert prog.info()["atomic_ops"] == 0
+    f_ref, (g_ref,) = OP.gradient(spec, [x])
+    assert srel(f.item(), f_ref) < TOL_F64_F and rel(g.cpu().numpy(), g_ref) < TOL_F64_G
+    f2, (g2,) = prog.run([to_dev(x)])
+    assert torch.equal(f, f2) and torch.equal(g, g2)
