@@ -460,8 +460,9 @@ pg_status pg_prog_run(pg_prog prog, const double* const* inputs, double* f_out,
                       double* const* grads, const double* fbar, pg_stream stream);
 /* What the transformation produced (filled by pg_prog_info, host out). */
 typedef struct {
-    int32_t fwd_kernels;      /* launches of the forward pass (shadow clearing not counted) */
-    int32_t rev_kernels;      /* launches of the reverse pass */
+    int32_t fwd_kernels;      /* launches of the forward pass (shadow clearing not counted);
+                                 three per scan until bound, then what its length takes */
+    int32_t rev_kernels;      /* launches of the reverse pass, likewise */
     int32_t atomic_ops;       /* reverse deliveries made atomic by the race rule (gathers) */
     int32_t rescheduled_ops;  /* reverse stencils rescheduled into gathers (no atomics), and,
                                  once bound, gathers delivered in transposed order */

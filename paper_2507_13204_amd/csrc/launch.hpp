@@ -405,6 +405,7 @@ struct ProgOpDev {
 hipError_t launch_prog_fwd(const ProgOpDev& o, hipStream_t s);
 hipError_t launch_prog_rev(const ProgOpDev& o, hipStream_t s);
 int64_t prog_scan_chunks(int64_t n);
+int prog_scan_launches(int64_t n);  // at most 3
 // Sets *flag nonzero unless offs[0] == 0, offs is non-decreasing and
 // offs[n_seg] == n.
 hipError_t launch_validate_offsets(const int64_t* offs, int64_t n_seg, int64_t n, int32_t* flag,
@@ -483,6 +484,10 @@ struct GatherRev {
     const int32_t* stale = nullptr;
     double* out = nullptr;
     int accumulate = 1;
+    // if f_out: the partials of f, summed into it on the way
+    const double* partials = nullptr;
+    int64_t n_partials = 0;
+    double* f_out = nullptr;
 };
 hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s);
 // Per incidence, part * n_nodes + entry: the part is the XCD that a group's

@@ -685,7 +685,7 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
             }
         } else {
             const Op& op = ops[(size_t)it.id];
-            const int32_t nk = op.kind == P_SCAN ? 3 : 1;  // a scan is three launches each way
+            const int32_t nk = op.kind == P_SCAN ? 3 : 1;  // a scan is up to three launches each way
             st.fwd_kernels += nk;
             if (!op.active) continue;
             st.rev_kernels += nk;
@@ -738,6 +738,12 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
     // lines, else scattered with the LDS table size and hash rotation chosen
     // for them.
     p->stats = p->planned_stats;
+    for (const Op& op : p->ops) {
+        if (!op.live || op.kind != P_SCAN) continue;
+        const int fewer = 3 - prog_scan_launches(op.n);
+        p->stats.fwd_kernels -= fewer;
+        if (op.active) p->stats.rev_kernels -= fewer;
+    }
     p->stored_first.assign(p->ops.size(), 0);
     PG_HIP(launch_zero(flag + 3, sizeof(int32_t), nullptr));  // no connectivity changed yet
     for (Group& g : p->groups) {
@@ -949,8 +955,10 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
         return d;
     };
 
-    // After a group's reverse: its gather's delivery through the transposed connectivity.
-    auto deliver_transposed = [&](int32_t gi) -> hipError_t {
+    // After a group's reverse: its gather's delivery through the transposed connectivity
+    // (with the sum of f's partials where that would be the next launch).
+    bool summed = false;
+    auto deliver_transposed = [&](int32_t gi, int64_t n_partials) -> hipError_t {
         const Group& g = p->groups[(size_t)gi];
         if (!g.transposed) return hipSuccess;
         const Op& go = ops[(size_t)g.gather];
@@ -967,6 +975,12 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
         r.stale = reinterpret_cast<const int32_t*>(p->ws + p->flag_off) + 3;
         r.out = shd[(size_t)go.a];
         r.accumulate = g.gather_first ? 0 : 1;
+        if (n_partials > 0 && r.n_nodes > 0) {
+            r.partials = partials;
+            r.n_partials = n_partials;
+            r.f_out = f_out ? f_out : at(p, p->fscratch_off);
+            summed = true;
+        }
         return launch_gather_rev(r, s);
     };
 
@@ -983,12 +997,12 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
             const GroupDev d = group_dev(it.id);
             if (it.id == p->sum_group) n_partials = group_blocks(n_sum, group_block_size(d, mode));
             PG_HIP(launch_group(d, mode, s));
-            if (mode == G_FWDREV) PG_HIP(deliver_transposed(it.id));
+            if (mode == G_FWDREV) PG_HIP(deliver_transposed(it.id, p->sum_ticket ? 0 : n_partials));
         } else {
             PG_HIP(launch_prog_fwd(op_dev(it.id), s));
         }
     }
-    if (!p->sum_ticket)
+    if (!p->sum_ticket && !summed)
         PG_HIP(launch_final_sum(partials, n_partials, f_out ? f_out : at(p, p->fscratch_off), s));
     if (!rev) return PG_OK;
     // Reverse pass: the schedule backwards, reads turned into deliveries.
@@ -1001,7 +1015,7 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
             for (int l = 0; l < d.n_leaves; ++l) any = any || d.leaf_shadow[l] != nullptr;
             if (any) {
                 PG_HIP(launch_group(d, G_REV, s));
-                PG_HIP(deliver_transposed(it.id));
+                PG_HIP(deliver_transposed(it.id, 0));
             }
         } else {
             const Op& op = ops[(size_t)it.id];

@@ -126,11 +126,19 @@ k_part_keys(const int32_t* __restrict__ conn, int64_t n_elems, int32_t k, int64_
 }
 
 // The same by element with atomics, for a connectivity changed since the
-// transposed one was built (nothing to do otherwise).
+// transposed one was built (nothing to do otherwise).  With f_out, the first
+// workgroup sums the partials of f instead, which saves that its launch.
 __global__ void __launch_bounds__(kBS) k_gather_scatter(GatherRev r) {
+    __shared__ double lds[16];
+    const unsigned first = r.f_out ? 1 : 0;
+    if (blockIdx.x < first) {
+        const double f = final_sum_block<false>(r.partials, r.n_partials, lds);
+        if (threadIdx.x == 0) *r.f_out = f;
+        return;
+    }
     if (!*r.stale) return;
-    for (int64_t e = (int64_t)blockIdx.x * kBS + threadIdx.x; e < r.n_elems;
-         e += (int64_t)gridDim.x * kBS) {
+    for (int64_t e = (int64_t)(blockIdx.x - first) * kBS + threadIdx.x; e < r.n_elems;
+         e += (int64_t)(gridDim.x - first) * kBS) {
         const double v = r.adj[e];
         for (int j = 0; j < r.k; ++j) atomic_add_f64(r.out + r.conn[e * r.k + j], r.B[e * r.k + j] * v);
     }
@@ -138,14 +146,22 @@ __global__ void __launch_bounds__(kBS) k_gather_scatter(GatherRev r) {
 
 // ------------------------------------------------------------ prefix scan
 //
-// Inclusive scan in three launches over chunks of kScanItems entries: chunk
-// totals, an exclusive scan of the totals by one workgroup, then each chunk's
-// local scan offset by its prefix.  With rev set, entry i is read and written
-// at n-1-i, which turns the prefix scan into the suffix scan of the reverse
-// pass: abar_j += sum_{i >= j} ybar_i.  Summation order is fixed.
+// Inclusive scan over chunks of kScanItems entries: chunk totals, then each
+// chunk's local scan offset by the sum of the totals before it.  Up to
+// kScanDirect chunks the workgroup of a chunk adds those itself (two launches,
+// one for a single chunk); beyond, one workgroup scans the totals in between.
+// With rev set, entry i is read and written at n-1-i, which turns the prefix
+// scan into the suffix scan of the reverse pass: abar_j += sum_{i >= j} ybar_i.
+// Summation order is fixed.  Bound by the launches up to some 10^5 entries, then
+// by memory.  A program of one scan and its reverse, us, with the middle launch
+// and each thread's run read straight from memory, with the chunks added
+// directly, and read by consecutive lanes as well: 1,000 entries 21, 12, 12; 10^6
+// 50, 45, 39; 8 10^6 227, 201, 137.  16 10^6: 432, 397, 288; 30 10^6 (14,649
+// chunks, the totals read 10^8 times): 821, 806, so the middle launch again.
 
 constexpr int kScanPer = 8;
 constexpr int kScanItems = kBS * kScanPer;
+constexpr int64_t kScanDirect = 8192;
 
 __device__ __forceinline__ int64_t scan_at(int64_t n, int64_t i, int rev) { return rev ? n - 1 - i : i; }
 
@@ -173,14 +189,31 @@ __device__ __forceinline__ double block_excl_scan(double v, double* lds, double*
     return off + (inc - v);
 }
 
+// The workgroup's sum of one value per thread, in every thread.
+__device__ __forceinline__ double block_sum_all(double v, double* lds) {
+    v = wave_sum(v);
+    if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = v;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kBS / kWave; ++w) t += lds[w];
+    __syncthreads();
+    return t;
+}
+
 __global__ void __launch_bounds__(kBS)
 k_scan_totals(int64_t n, const double* __restrict__ a, int rev, double* __restrict__ totals) {
     __shared__ double lds[kBS / kWave];
-    const int64_t base = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
+    const int64_t base = (int64_t)blockIdx.x * kScanItems + threadIdx.x;
+    double v[kScanPer];
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        const int64_t i = base + q * kBS;
+        v[q] = i < n ? a[scan_at(n, i, rev)] : 0.0;
+    }
     double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < kScanPer; ++q)
-        if (base + q < n) s += a[scan_at(n, base + q, rev)];
+    for (int q = 0; q < kScanPer; ++q) s += v[q];
     const double t = block_sum<kBS>(s, lds);
     if (threadIdx.x == 0) totals[blockIdx.x] = t;
 }
@@ -199,41 +232,72 @@ k_scan_top(int64_t nchunks, double* __restrict__ totals) {
     }
 }
 
-// accumulate 0: y = scan; 1: y += scan.
+// DIRECT: totals holds the chunk totals; else their exclusive scan.
+// accumulate 0: y = scan; 1: y += scan.  Consecutive lanes read and write
+// consecutive entries; in between each thread scans kScanPer consecutive ones,
+// turned through LDS (one pad entry per thread's run).
+template <bool DIRECT>
 __global__ void __launch_bounds__(kBS)
-k_scan_apply(int64_t n, const double* __restrict__ a, int rev, const double* __restrict__ prefix,
+k_scan_apply(int64_t n, const double* __restrict__ a, int rev, const double* __restrict__ totals,
              double* __restrict__ y, int accumulate) {
     __shared__ double lds[kBS / kWave];
-    const int64_t base = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
-    double v[kScanPer];
+    __shared__ double turn[kBS * (kScanPer + 1)];
+    const int tid = threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * kScanItems + tid;
+    double v[kScanPer], was[kScanPer];
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        const int64_t i = base + q * kBS;
+        v[q] = i < n ? a[scan_at(n, i, rev)] : 0.0;
+        was[q] = accumulate && i < n ? y[scan_at(n, i, rev)] : 0.0;
+    }
+    double before = 0.0;
+    if constexpr (DIRECT) {
+        for (unsigned q = tid; q < blockIdx.x; q += kBS) before += totals[q];
+        before = block_sum_all(before, lds);
+    } else {
+        before = totals[blockIdx.x];
+    }
+    const int at = tid / kScanPer * (kScanPer + 1) + tid % kScanPer;  // of entry q * kBS + tid
+    constexpr int kStep = kBS / kScanPer * (kScanPer + 1);
+    double* const mine = turn + tid * (kScanPer + 1);
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) turn[q * kStep + at] = v[q];
+    __syncthreads();
     double s = 0.0;
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
-        v[q] = base + q < n ? a[scan_at(n, base + q, rev)] : 0.0;
+        v[q] = mine[q];
         s += v[q];
     }
     double tot;
-    double run = prefix[blockIdx.x] + block_excl_scan(s, lds, &tot);
+    double run = before + block_excl_scan(s, lds, &tot);
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
         run += v[q];
-        if (base + q < n) {
-            const int64_t j = scan_at(n, base + q, rev);
-            if (accumulate)
-                y[j] += run;
-            else
-                y[j] = run;
-        }
+        mine[q] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        const int64_t i = base + q * kBS;
+        const double r = turn[q * kStep + at];
+        if (i < n) y[scan_at(n, i, rev)] = accumulate ? was[q] + r : r;
     }
 }
 
 hipError_t launch_scan(int64_t n, const double* a, int rev, double* scratch, double* y,
                        int accumulate, hipStream_t s) {
-    const int64_t nchunks = (n + kScanItems - 1) / kScanItems;
-    hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)nchunks), dim3(kBS), 0, s, n, a, rev, scratch);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBS), 0, s, nchunks, scratch);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nchunks), dim3(kBS), 0, s, n, a, rev, scratch,
-                       y, accumulate);
+    const int64_t nchunks = prog_scan_chunks(n);
+    const dim3 grid((unsigned)nchunks), block(kBS);
+    if (nchunks > 1)
+        hipLaunchKernelGGL(k_scan_totals, grid, block, 0, s, n, a, rev, scratch);
+    if (nchunks <= kScanDirect) {
+        hipLaunchKernelGGL(k_scan_apply<true>, grid, block, 0, s, n, a, rev, scratch, y, accumulate);
+    } else {
+        hipLaunchKernelGGL(k_scan_top, dim3(1), block, 0, s, nchunks, scratch);
+        hipLaunchKernelGGL(k_scan_apply<false>, grid, block, 0, s, n, a, rev, scratch, y, accumulate);
+    }
     return hipGetLastError();
 }
 
@@ -759,6 +823,13 @@ hipError_t launch_group_ns(const GroupDev& g, int mode, hipStream_t s) {
 
 }  // namespace
 
+int64_t prog_scan_chunks(int64_t n) { return (n + kScanItems - 1) / kScanItems; }
+
+int prog_scan_launches(int64_t n) {
+    const int64_t c = prog_scan_chunks(n);
+    return c <= 1 ? (int)c : c <= kScanDirect ? 2 : 3;
+}
+
 int64_t group_blocks(int64_t n, int bs) { return (n + bs - 1) / bs; }
 
 // A group with a fused gather scatters through the LDS table in its reverse
@@ -804,7 +875,8 @@ hipError_t launch_gather_rev(const GatherRev& r, hipStream_t s) {
         PG_LAUNCH(k_gather_rev<kXcds>, grid, block, 0, s, r);
     else
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gather_scatter, dim3(std::min(nblocks(r.n_elems), 256u)), block, 0, s, r);
+    const unsigned scatter = std::min(nblocks(r.n_elems), 256u) + (r.f_out ? 1u : 0u);
+    hipLaunchKernelGGL(k_gather_scatter, dim3(scatter), block, 0, s, r);
     return hipGetLastError();
 }
 
@@ -840,8 +912,6 @@ hipError_t launch_prog_rev(const ProgOpDev& o, hipStream_t s) {
     }
     return hipGetLastError();
 }
-
-int64_t prog_scan_chunks(int64_t n) { return (n + kScanItems - 1) / kScanItems; }
 
 hipError_t launch_validate_offsets(const int64_t* offs, int64_t n_seg, int64_t n, int32_t* flag,
                                    hipStream_t s) {
