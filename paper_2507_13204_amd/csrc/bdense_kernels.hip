@@ -11,7 +11,8 @@
 // longer accumulation is FP64.  A wave
 // loads its operand fragments from global memory straight into the registers
 // the instruction reads, a k-step or more ahead, so there is no LDS staging
-// and no barrier in the k loop; the nonlinearity and its derivative are fused
+// and no barrier in the k loop (but for the split of large FP32 tiles, whose
+// waves share it); the nonlinearity and its derivative are fused
 // into the forward epilogue, so neither Y nor psi(Y) round-trips through HBM;
 // the objective is reduced per tile and then in a fixed order (deterministic).
 #include <type_traits>
@@ -153,8 +154,9 @@ struct Frag {
 //
 // Bound by the matrix cores in FP64 (66 TFLOP/s of 78.6 at 4096 x 1024, 59 with
 // the tiles staged through LDS and a barrier per k-step), by the vector
-// instructions of the split and the FP64 sums in FP32 (118 TFLOP/s, 100 on
-// v_mfma_f32_16x16x4_f32 through LDS), and by latency below some 500 x 500:
+// instructions of the split and the FP64 sums in FP32 (151 TFLOP/s; 118 with
+// every wave splitting all its operands, 100 on v_mfma_f32_16x16x4_f32 through
+// LDS; 3,000 x 500, a gradient: 186 us, 218 unshared), and by latency below some 500 x 500:
 // 257 x 129 takes 13 us per gradient (106 / 81 before, in 128 x 128 tiles).
 template <typename T, int AR, bool TRANS_A, int EPI, typename S>
 __global__ void __launch_bounds__(S::NTHR, S::OCC)
@@ -173,6 +175,12 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
     constexpr int kBase = AR == FP32 ? 1 : E, kStep = AR == FP32 ? 4 : 1;
     constexpr bool kWide = AR != FP64;
     using F = Frag<T, E, BX, BY>;
+    // SPLIT, as many waves side by side as A blocks to a wave: they have the
+    // same A rows, and each splits one block for all of them, through LDS.
+    constexpr bool kShare = AR == SPLIT && BX == 4 && S::WN == BX;
+    constexpr int kPartBytes = KW > 1 ? KW * S::WM * S::WN * BX * BY * 4 * 64 * 8 : 16;
+    constexpr int kShareBytes = kShare ? KW * S::WM * 2 * BX * (int)sizeof(Split) * 64 : 16;
+    __shared__ alignas(16) unsigned char smem[kPartBytes > kShareBytes ? kPartBytes : kShareBytes];
     __shared__ double red[16];
     // Backward: a workgroup past the tiles sums the forward's partials of f.
     const uint32_t tiles = gridDim.x - (EPI == EPI_BWD && f_out ? 1 : 0);
@@ -296,9 +304,86 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
                 }
         }
     };
-    if (any) {
+    const int64_t n = t1 - t0;
+    if constexpr (kShare) {
+        // One barrier per k-step.  Between two of them a wave multiplies step t
+        // while it splits its share of step t + 1 into the other buffer and
+        // loads step t + 2.  Every wave takes every barrier, also one past the
+        // edge of C (it reads the last whole block) and one whose part of K is
+        // a step shorter.
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const int xs = wmn % S::WN;
+        u4* const shared_a = reinterpret_cast<u4*>(smem) + (int64_t)(kw * S::WM + wmn / S::WN) * 2 * BX * 3 * 64 + lane;
+        const T* const own = TRANS_A ? pa[0] + xs : A + low(i0 + 16 * xs + li, M - 1) * K + (kbeg + kBase * lk);
+        float ra[E], rb[E][BY];
+        Split sb[BY];
+        auto load1 = [&](int64_t t) {
+            const int64_t k = t * KS;
+            if constexpr (TRANS_A) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) ra[e] = own[(k + e) * M];
+            } else {
+                load_vec<T, E>(own + k, ra);
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) load_vec(pb + (k + e) * N, rb[e]);
+        };
+        auto share = [&](int64_t t, Split (&o)[BY]) {
+            const Split a = split3(ra);
+            u4* const q = shared_a + ((t & 1) * BX + xs) * 3 * 64;
+            q[0] = u4{a.h[0], a.h[1], a.h[2], a.h[3]};
+            q[64] = u4{a.m[0], a.m[1], a.m[2], a.m[3]};
+            q[128] = u4{a.l[0], a.l[1], a.l[2], a.l[3]};
+#pragma unroll
+            for (int y = 0; y < BY; ++y) {
+                float v[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) v[e] = rb[e][y];
+                o[y] = split3(v);
+            }
+        };
+        auto multiply = [&](int64_t t) {
+#pragma unroll
+            for (int x = 0; x < BX; ++x) {
+                const u4* const q = shared_a + ((t & 1) * BX + x) * 3 * 64;
+                const u4 h = q[0], m = q[64], l = q[128];
+                const Split a{{h[0], h[1], h[2], h[3]}, {m[0], m[1], m[2], m[3]}, {l[0], l[1], l[2], l[3]}};
+#pragma unroll
+                for (int y = 0; y < BY; ++y) {
+                    const f4 c = mma_split(a, sb[y]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)c[r];
+                }
+            }
+        };
+        const int64_t nmin = steps / KW, nmax = (steps + KW - 1) / KW;
+        if (n > 0) {
+            load1(0);
+            share(0, sb);
+            if (n > 1) load1(1);
+        }
+        __syncthreads();
+        int64_t t = 0;
+        for (; t + 2 < nmin; ++t) {
+            Split next[BY];
+            share(t + 1, next);
+            load1(t + 2);
+            multiply(t);
+#pragma unroll
+            for (int y = 0; y < BY; ++y) sb[y] = next[y];
+            __syncthreads();
+        }
+        for (; t < nmax; ++t) {
+            Split next[BY] = {};
+            if (t + 1 < n) share(t + 1, next);
+            if (t + 2 < n) load1(t + 2);
+            if (t < n) multiply(t);
+#pragma unroll
+            for (int y = 0; y < BY; ++y) sb[y] = next[y];
+            __syncthreads();
+        }
+    } else if (any) {
         F f[D];
-        const int64_t n = t1 - t0;
 #pragma unroll
         for (int d = 0; d < D; ++d)
             if (d < n) load(f[d], d);
@@ -316,6 +401,8 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
 #pragma unroll
         for (int d = 0; d < D; ++d)
             if (t + d + D < n) mma(f[d], [] {});
+    }
+    if (any) {
         if (t1 * KS < kend) {
             // the last K % KS products: k past the end contributes zero
             const int64_t k0 = n * KS;
@@ -408,7 +495,8 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
         // The KW partial sums of each entry, added in ascending k order; the
         // entries are dealt to all the waves.
         constexpr int NS = S::WM * S::WN * BX * BY * 4;  // 64-entry slices of the tile
-        __shared__ double part[KW][NS][64];
+        static_assert(KW * NS * 64 * 8 == kPartBytes, "room for the partial sums");
+        double(*const part)[NS][64] = reinterpret_cast<double(*)[NS][64]>(smem);
 #pragma unroll
         for (int x = 0; x < BX; ++x)
 #pragma unroll
@@ -463,7 +551,7 @@ Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SP
 // cost: picoseconds per product and entry of a tile with every compute unit
 // busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.
 constexpr ShapeInfo kShapes[] = {
-    info<S0>(7.7, 5.8, 4.3),   info<S1>(7.8, 5.8, 4.5),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.2),
+    info<S0>(7.7, 5.8, 3.4),   info<S1>(7.8, 5.8, 3.75),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.2),
     info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 8.9), info<S6>(22.7, 11.0, 11.4)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
@@ -476,9 +564,9 @@ int64_t tiles_of(const BDenseView& b, int sh) {
 
 // The shape with the least time for its rounds of 256 tiles, one to a compute
 // unit.  Measured gradients that the rule decides (FP64 / FP32, us): 3,000 x
-// 500: 725 / 403 in 128 x 128 tiles (96 of them), 373 / 218 in 64 x 128 (188),
-// 334 / 230 in 64 x 32 (752); 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
-// 32 x 16; 4,096 x 1,024: 1,043 / 588 in 128 x 128, 1,189 / 730 in 64 x 64.
+// 500: 725 / 342 in 128 x 128 tiles (96 of them), 373 / 186 in 64 x 128 (188),
+// 334 / 208 in 64 x 32 (752); 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
+// 32 x 16; 4,096 x 1,024: 1,043 / 454 in 128 x 128, 1,189 / 692 in 64 x 64.
 int bdense_shape(const BDenseView& b) {
     int best = kNShapes - 1;
     double tbest = 1e300;
