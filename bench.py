@@ -81,6 +81,12 @@ HEX_KERNELS = {
 }
 
 
+def _f32_peak(m: int, n: int) -> float:
+    """TFLOP/s of the unit that the FP32 products of this size run on: the FP32
+    matrix instruction, or (from 2^20 entries) six bfloat16 products for each."""
+    return 157.3 if m * n < 1 << 20 else round(2500 / 6, 1)
+
+
 def traffic_record(kernel_key: str):
     """HBM bytes per launch of the dominant kernel, measured with rocprofv3
     byte counters (profiles/traffic.json), or None if the kernel sources have
@@ -503,7 +509,7 @@ def _other_configs(args):
     m_, n_ = args.bd_m, args.bd_n
     b = inputs.batched_dense(m_, n_)
     flop = 2.0 * m_ * m_ * n_
-    for dt, tdt, peak in (("f64", torch.float64, 78.6), ("f32", torch.float32, 157.3)):
+    for dt, tdt, peak in (("f64", torch.float64, 78.6), ("f32", torch.float32, _f32_peak(m_, n_))):
         A = torch.from_numpy(b.A).to(dev, tdt)
         W = torch.from_numpy(b.W).to(dev, tdt)
         X = torch.from_numpy(b.X).to(dev, tdt)
@@ -516,7 +522,7 @@ def _other_configs(args):
         k_f = _hook_ms(o, lambda: o.objective(X), steps)
         res[f"bdense_{dt}"] = {
             "workload": f"batched dense A {m_}x{m_}, X {m_}x{n_}, {dt} matrix cores"
-                        + (", each 16-deep k-tile added into FP64" if dt == "f32" else ""),
+                        + (", operands in three bfloat16 parts, each 32-deep k-step added into FP64" if dt == "f32" else ""),
             "forward_kernel_ms": round(k_f, 5),
             "forward_TFLOPs": round(flop / (k_f * 1e-3) / 1e12, 3),
             "forward_frac_peak": round(flop / (k_f * 1e-3) / 1e12 / peak, 4),
@@ -630,7 +636,7 @@ def bench_dense(args):
     cpu_s = time.perf_counter() - t0
     _line("dense row-reduction gradient GB/s (A n x n, one pass over A)", gbytes / (ms_g * 1e-3),
           "GB/s", args, ms_g, args.dtype,
-          {"workload": f"dense {n}x{n} {args.dtype}, one workgroup team per row band"},
+          {"workload": f"dense {n}x{n} {args.dtype}, one pass over A for f and the gradient"},
           gradient_over_objective=round(ms_g / ms_f, 4), objective_ms=round(ms_f, 5),
           roofline={"bound": "hbm", "achieved": round(gbytes / (k_g * 1e-3), 2),
                     "peak": PEAK_HBM_GBS, "unit": "GB/s",
@@ -667,7 +673,7 @@ def bench_bdense(args):
                      "fwd_plus_bwd_over_fwd": round((ms_f + ms_b) / ms_f, 4)}
         obj.close()
     flop = 2.0 * m * m * n
-    peak = 78.6 if args.dtype == "f64" else 157.3
+    peak = 78.6 if args.dtype == "f64" else _f32_peak(m, n)
     kf = res["store"]["fwd_kernel_ms"]
     Xs = np.ascontiguousarray(b.X[:, :64])
     t0 = time.perf_counter()
