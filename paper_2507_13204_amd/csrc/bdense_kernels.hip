@@ -156,7 +156,7 @@ struct Frag {
 // the tiles staged through LDS and a barrier per k-step), by the vector
 // instructions of the split and the FP64 sums in FP32 (151 TFLOP/s; 118 with
 // every wave splitting all its operands, 100 on v_mfma_f32_16x16x4_f32 through
-// LDS; 3,000 x 500, a gradient: 186 us, 218 unshared), and by latency below some 500 x 500:
+// LDS; 3,000 x 500, a gradient: 168 us, 218 unshared), and by latency below some 500 x 500:
 // 257 x 129 takes 13 us per gradient (106 / 81 before, in 128 x 128 tiles).
 template <typename T, int AR, bool TRANS_A, int EPI, typename S>
 __global__ void __launch_bounds__(S::NTHR, S::OCC)
@@ -175,9 +175,11 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
     constexpr int kBase = AR == FP32 ? 1 : E, kStep = AR == FP32 ? 4 : 1;
     constexpr bool kWide = AR != FP64;
     using F = Frag<T, E, BX, BY>;
-    // SPLIT, as many waves side by side as A blocks to a wave: they have the
-    // same A rows, and each splits one block for all of them, through LDS.
-    constexpr bool kShare = AR == SPLIT && BX == 4 && S::WN == BX;
+    // SPLIT, at least as many waves side by side as A blocks to a wave: they
+    // have the same A rows, and BX of them split one block each for all, through
+    // LDS.
+    constexpr bool kShare = AR == SPLIT && BX > 2 && S::WN >= BX;
+    static_assert(BX != 3 || kShare, "blocks of three rows only where they are read one by one");
     constexpr int kPartBytes = KW > 1 ? KW * S::WM * S::WN * BX * BY * 4 * 64 * 8 : 16;
     constexpr int kShareBytes = kShare ? KW * S::WM * 2 * BX * (int)sizeof(Split) * 64 : 16;
     __shared__ alignas(16) unsigned char smem[kPartBytes > kShareBytes ? kPartBytes : kShareBytes];
@@ -314,26 +316,32 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
         typedef uint32_t u4 __attribute__((ext_vector_type(4)));
         const int xs = wmn % S::WN;
         u4* const shared_a = reinterpret_cast<u4*>(smem) + (int64_t)(kw * S::WM + wmn / S::WN) * 2 * BX * 3 * 64 + lane;
-        const T* const own = TRANS_A ? pa[0] + xs : A + low(i0 + 16 * xs + li, M - 1) * K + (kbeg + kBase * lk);
+        const bool splits_a = xs < BX;
+        const int xa = splits_a ? xs : 0;
+        const T* const own = TRANS_A ? pa[0] + xa : A + low(i0 + 16 * xa + li, M - 1) * K + (kbeg + kBase * lk);
         float ra[E], rb[E][BY];
         Split sb[BY];
         auto load1 = [&](int64_t t) {
             const int64_t k = t * KS;
-            if constexpr (TRANS_A) {
+            if (BX == S::WN || splits_a) {
+                if constexpr (TRANS_A) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) ra[e] = own[(k + e) * M];
-            } else {
-                load_vec<T, E>(own + k, ra);
+                    for (int e = 0; e < E; ++e) ra[e] = own[(k + e) * M];
+                } else {
+                    load_vec<T, E>(own + k, ra);
+                }
             }
 #pragma unroll
             for (int e = 0; e < E; ++e) load_vec(pb + (k + e) * N, rb[e]);
         };
         auto share = [&](int64_t t, Split (&o)[BY]) {
-            const Split a = split3(ra);
-            u4* const q = shared_a + ((t & 1) * BX + xs) * 3 * 64;
-            q[0] = u4{a.h[0], a.h[1], a.h[2], a.h[3]};
-            q[64] = u4{a.m[0], a.m[1], a.m[2], a.m[3]};
-            q[128] = u4{a.l[0], a.l[1], a.l[2], a.l[3]};
+            if (BX == S::WN || splits_a) {
+                const Split a = split3(ra);
+                u4* const q = shared_a + ((t & 1) * BX + xs) * 3 * 64;
+                q[0] = u4{a.h[0], a.h[1], a.h[2], a.h[3]};
+                q[64] = u4{a.m[0], a.m[1], a.m[2], a.m[3]};
+                q[128] = u4{a.l[0], a.l[1], a.l[2], a.l[3]};
+            }
 #pragma unroll
             for (int y = 0; y < BY; ++y) {
                 float v[E];
@@ -531,6 +539,7 @@ using S3 = Shape<2, 2, 2, 1, 4, 1, 1, 4>;  // 64 x 32
 using S4 = Shape<2, 2, 1, 1, 8, 1, 1, 4>;  // 32 x 32
 using S5 = Shape<2, 1, 1, 1, 8, 3, 2, 2>;  // 32 x 16
 using S6 = Shape<1, 1, 1, 1, 8, 4, 2, 2>;  // 16 x 16, the one that takes any size
+using S7 = Shape<3, 2, 1, 4, 2, 2, 1, 2>;  // 48 x 128, split FP32 operands only
 struct ShapeInfo {
     int tm, tn, bx, by;
     double cost[3];  // by Arith
@@ -552,7 +561,8 @@ Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SP
 // busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.
 constexpr ShapeInfo kShapes[] = {
     info<S0>(7.7, 5.8, 3.4),   info<S1>(7.8, 5.8, 3.75),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.2),
-    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 8.9), info<S6>(22.7, 11.0, 11.4)};
+    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 8.9), info<S6>(22.7, 11.0, 11.4),
+    info<S7>(1e9, 1e9, 3.9)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 int64_t tiles_of(const BDenseView& b, int sh) {
@@ -565,10 +575,11 @@ int64_t tiles_of(const BDenseView& b, int sh) {
 // The shape with the least time for its rounds of 256 tiles, one to a compute
 // unit.  Measured gradients that the rule decides (FP64 / FP32, us): 3,000 x
 // 500: 725 / 342 in 128 x 128 tiles (96 of them), 373 / 186 in 64 x 128 (188),
-// 334 / 208 in 64 x 32 (752); 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
+// - / 168 in 48 x 128 (252: one to nearly every compute unit), 334 / 209 in 64 x
+// 32 (752); 2,000 x 700, FP32: 135 in 64 x 128, 121 in 48 x 128; 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
 // 32 x 16; 4,096 x 1,024: 1,043 / 454 in 128 x 128, 1,189 / 692 in 64 x 64.
 int bdense_shape(const BDenseView& b) {
-    int best = kNShapes - 1;
+    int best = 6;
     double tbest = 1e300;
     for (int i = 0; i < kNShapes; ++i) {
         const ShapeInfo& s = kShapes[i];
@@ -609,6 +620,9 @@ hipError_t launch_gemm(const BDenseView& b, hipStream_t s, const T* A, const T* 
         case 4: return launch_shape<T, AR, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 5: return launch_shape<T, AR, TRANS, EPI, S5>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 6: return launch_shape<T, AR, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 7:
+            if constexpr (AR == SPLIT)
+                return launch_shape<T, AR, TRANS, EPI, S7>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
     }
     return hipErrorInvalidValue;
 }

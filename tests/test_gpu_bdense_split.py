@@ -17,9 +17,9 @@ F32_F, F32_G = 1e-7, 3e-7
 
 # (rows and contraction, columns): steps of 32 even and odd in number, with no,
 # one and 31 terms left; columns that end within a wave's block, a wave's tile
-# and a tile; tiles of 128 x 128 (4065), 64 x 128 and 32 x 32 (2048 x 520).
+# and a tile; tiles of 128 x 128 (4065), 64 x 128, 48 x 128 (3000, 2999) and 32 x 32 (2048 x 520).
 @pytest.mark.parametrize("m,n", [(1024, 1024), (1056, 1000), (1087, 970), (1181, 900), (1345, 801),
-                                 (2048, 520), (3000, 500), (4065, 1000)])
+                                 (2048, 520), (3000, 500), (2999, 497), (4065, 1000)])
 def test_bdense_split_edges(m, n):
     from paper_2507_13204_amd import BatchedDense
     b = inputs.batched_dense(m, n, seed=m)
