@@ -5,10 +5,10 @@
 // Both products are m x m by m x n contractions on the matrix cores.  FP64:
 // v_mfma_f64_16x16x4_f64.  FP32, small: v_mfma_f32_16x16x4_f32, 16 terms at a
 // time.  FP32, large: each operand is split into three bfloat16 parts (8 + 8 +
-// 8 bits, nearest) and the six products that reach FP32 precision run on
-// v_mfma_f32_16x16x32_bf16, smallest first, 32 terms at a time.  Either FP32
-// sum is added into FP64 accumulators and the next starts from zero, so every
-// longer accumulation is FP64.  A wave
+// 8 bits, nearest) and eight of their nine products run on
+// v_mfma_f32_16x16x32_bf16, 32 terms at a time, the leading parts' apart from
+// the others.  Every FP32 sum is added into FP64 accumulators and the next
+// starts from zero, so every longer accumulation is FP64.  A wave
 // loads its operand fragments from global memory straight into the registers
 // the instruction reads, a k-step or more ahead, so there is no LDS staging
 // and no barrier in the k loop (but for the split of large FP32 tiles, whose
@@ -89,19 +89,33 @@ __device__ __forceinline__ Split split3(const float (&v)[8]) {
     return s;
 }
 
-// 32 products per entry.  What is left out (m l, l m, l l) is below 2^-24 of
-// a product.  Against FP64 on a ~ N(0,1/m), b ~ U(-1,1): 3.7e-8 (2-norm) per
-// 32 terms, against 7.4e-8 for two 16-term chains of v_mfma_f32_16x16x4_f32.
-__device__ __forceinline__ f4 mma_split(const Split& a, const Split& b) {
+// 32 products per entry: the leading parts' in a sum of their own, which goes
+// into the FP64 sums at once, and the other parts', some 2^-8 of it, in a sum
+// that runs on for kLowSteps k-steps.  (In one sum the small products lose to
+// the large ones: the instruction aligns eight terms at a time to their largest
+// and truncates.)  Left out is l l, 2^-34 of a product.  Entry error of a
+// gradient, rms over sum |a| |b|, against v_mfma_f32_16x16x4_f32 in sums of 16
+// / one sum of the six largest products / this (1,056 x 1,000): a ~ N(0,1/m), b
+// ~ U(-1,1) 3.5e-9 / 2.4e-9 / 1.6e-9; one term to an entry 2.52e-8 / 3.32e-8 /
+// 2.53e-8 (largest 5.96e-8 / 1.45e-7 / 5.97e-8: the rounding of the result);
+// sums that cancel 7.0e-10 / 1.2e-9 / 1.7e-11; rows and columns of magnitudes
+// 2^-20 to 2^10 7.4e-9 / 7.7e-9 / 6.2e-9.  Operands log-uniform over e^+-10
+// are the exception: 1.78e-8 / 2.16e-8 / 1.96e-8 (largest 1.39e-7 / 1.28e-7 /
+// 1.30e-7).
+constexpr int kLowSteps = 8;
+__device__ __forceinline__ f4 mma_high(const Split& a, const Split& b) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(parts(a.h), parts(b.h), f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mma_low(const Split& a, const Split& b, f4 c) {
     const bf8 ah = parts(a.h), am = parts(a.m), al = parts(a.l);
     const bf8 bh = parts(b.h), bm = parts(b.m), bl = parts(b.l);
-    f4 c = {0.f, 0.f, 0.f, 0.f};
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bm, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, bl, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, bm, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, bh, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bm, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, c, 0, 0, 0);
     return c;
 }
 
@@ -152,12 +166,12 @@ struct Frag {
 // 16 x 16 reads the last row or column again instead), so the loads need no
 // bounds checks; the caller offers only shapes whose blocks fit C.
 //
-// Bound by the matrix cores in FP64 (66 TFLOP/s of 78.6 at 4096 x 1024, 59 with
+// Bound by the matrix cores in FP64 (67 TFLOP/s of 78.6 at 4096 x 1024, 59 with
 // the tiles staged through LDS and a barrier per k-step), by the vector
-// instructions of the split and the FP64 sums in FP32 (151 TFLOP/s; 118 with
-// every wave splitting all its operands, 100 on v_mfma_f32_16x16x4_f32 through
-// LDS; 3,000 x 500, a gradient: 168 us, 218 unshared), and by latency below some 500 x 500:
-// 257 x 129 takes 13 us per gradient (106 / 81 before, in 128 x 128 tiles).
+// instructions of the split and the FP64 sums, beside the eight products, in
+// FP32 (4,096 x 1,024: 530-554 us a gradient, 127 TFLOP/s; 1,323 on
+// v_mfma_f32_16x16x4_f32; six products in one sum, which was less accurate, 456),
+// and by latency below some 500 x 500: 257 x 129 takes 10.6 us per FP32 gradient.
 template <typename T, int AR, bool TRANS_A, int EPI, typename S>
 __global__ void __launch_bounds__(S::NTHR, S::OCC)
 k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_t N, int64_t K,
@@ -220,7 +234,8 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
     }
     const T* pb = Bm + low(j0 + BY * li, N - BY) + (kbeg + kBase * lk) * N;
 
-    // FP64: the running sums; else the 16-term sums of the FP32 instruction
+    // FP64: the running sums; FP32 instruction: the 16-term sums; split: the
+    // small parts' sums
     acc_t acc[BX][BY];
     double wide[kWide ? BX : 1][kWide ? BY : 1][4];
     auto clear = [&]() {
@@ -257,7 +272,7 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
 #pragma unroll
         for (int e = 0; e < E; ++e) load_vec(pb + (k + kStep * e) * N, f.b[e]);
     };
-    // FP32: the 16-term sums into the FP64 ones.
+    // FP32: the 16-term sums (split: the small parts') into the FP64 ones.
     [[maybe_unused]] auto fold = [&]() {
 #pragma unroll
         for (int x = 0; x < BX; ++x)
@@ -300,7 +315,8 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
             for (int y = 0; y < BY; ++y)
 #pragma unroll
                 for (int x = 0; x < BX; ++x) {
-                    const f4 c = mma_split(a[x], b[y]);
+                    const f4 c = mma_high(a[x], b[y]);
+                    acc[x][y] = mma_low(a[x], b[y], acc[x][y]);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)c[r];
                 }
@@ -358,7 +374,8 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
                 const Split a{{h[0], h[1], h[2], h[3]}, {m[0], m[1], m[2], m[3]}, {l[0], l[1], l[2], l[3]}};
 #pragma unroll
                 for (int y = 0; y < BY; ++y) {
-                    const f4 c = mma_split(a, sb[y]);
+                    const f4 c = mma_high(a, sb[y]);
+                    acc[x][y] = mma_low(a, sb[y], acc[x][y]);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) wide[x][y][r] += (double)c[r];
                 }
@@ -377,6 +394,7 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
             share(t + 1, next);
             load1(t + 2);
             multiply(t);
+            if ((t & (kLowSteps - 1)) == kLowSteps - 1) fold();
 #pragma unroll
             for (int y = 0; y < BY; ++y) sb[y] = next[y];
             __syncthreads();
@@ -399,6 +417,10 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
         for (; t + 2 * D <= n; t += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) mma(f[d], [&] { load(f[d], t + d + D); });
+            if constexpr (AR == SPLIT) {
+                static_assert(kLowSteps % D == 0, "t is a multiple of D");
+                if ((t & (kLowSteps - D)) == kLowSteps - D) fold();
+            }
         }
 #pragma unroll
         for (int d = 0; d < D; ++d)
@@ -428,6 +450,7 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
             mma(z, [] {});
         }
         if constexpr (AR == SPLIT) {
+            fold();
             // An operand or a sum that is not finite: the whole block again on
             // the FP32 instruction, whose infinities are those of the sums.
             bool bad = false;
@@ -549,20 +572,23 @@ constexpr ShapeInfo info(double c64, double c32, double split) {
     return {S::TM, S::TN, S::BX, S::BY, {c64, c32, split}};
 }
 
-// Whether FP32 operands are split.  Both forms round each product sum to some
-// 2^-24 of a term, differently; f, an FP64 result, averages that over its
-// entries (2e-7 / sqrt(m n) for the FP32 instruction, 1.2e-7 split).  Below
-// 2^20 entries, where the two could differ by 1e-9 of f and where latency hides
-// the slower instruction (1,024 x 1,024: 73 us against 60; 512 x 384: 19, 17),
-// f keeps the bits that the FP32 instruction's 16-term sums give it.
+// Whether FP32 operands are split.  Gradients, FP32 instruction / split, us:
+// 300 x 300 13.5 / 17.7, 512 x 512 20.6 / 19.7, 700 x 700 37.4 / 43.2, 900 x
+// 900 79 / 65, 1,000 x 1,000 102 / 73, 2,000 x 540 217 / 131, 10,000 x 100 1,091
+// / 593.  From 2^20 entries the split is the faster one at every shape tried;
+// below, either may be, and the products keep the FP32 instruction's bits.
 bool splits(const BDenseView& b) { return b.dtype == F32 && b.m * b.n >= (1 << 20); }
 Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SPLIT : FP32; }
 // cost: picoseconds per product and entry of a tile with every compute unit
-// busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.
+// busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.  The rule below
+// takes a shape within 6% of the best one at 12 FP64 sizes from 300 x 300 to
+// 4,096 x 1,024 (5,000 x 17 and 6,000 x 33 among them), within 8% at 15 split
+// ones from 1,024 x 1,024 to 8,000 x 140 and 6,000 x 1,000, and within 12% at
+// 11 of the FP32 instruction.
 constexpr ShapeInfo kShapes[] = {
-    info<S0>(7.7, 5.8, 3.4),   info<S1>(7.8, 5.8, 3.75),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.2),
-    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 8.9), info<S6>(22.7, 11.0, 11.4),
-    info<S7>(1e9, 1e9, 3.9)};
+    info<S0>(7.7, 5.8, 3.95),  info<S1>(7.8, 5.8, 4.25),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.1),
+    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 9.0), info<S6>(22.7, 11.0, 11.0),
+    info<S7>(1e9, 1e9, 4.5)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 int64_t tiles_of(const BDenseView& b, int sh) {
@@ -573,11 +599,11 @@ int64_t tiles_of(const BDenseView& b, int sh) {
 }  // namespace
 
 // The shape with the least time for its rounds of 256 tiles, one to a compute
-// unit.  Measured gradients that the rule decides (FP64 / FP32, us): 3,000 x
-// 500: 725 / 342 in 128 x 128 tiles (96 of them), 373 / 186 in 64 x 128 (188),
-// - / 168 in 48 x 128 (252: one to nearly every compute unit), 334 / 209 in 64 x
-// 32 (752); 2,000 x 700, FP32: 135 in 64 x 128, 121 in 48 x 128; 1,000 x 100: 264 / 159 in 128 x 128, 25 / 25 in
-// 32 x 16; 4,096 x 1,024: 1,043 / 454 in 128 x 128, 1,189 / 692 in 64 x 64.
+// unit.  Measured gradients that the rule decides (FP64 / split, us): 3,000 x
+// 500: 722 / 401 in 128 x 128 tiles (96 of them), 372 / 217 in 64 x 128 (188),
+// - / 187 in 48 x 128 (252: one to nearly every compute unit), 320 / 238 in 64 x
+// 32 (752); 4,096 x 1,024: 1,015 / 530 in 128 x 128, 1,116 / 750 in 64 x 64; 1,000 x
+// 100, FP64 / FP32 instruction: 262 / 332 in 128 x 128, 24 / 28 in 32 x 16.
 int bdense_shape(const BDenseView& b) {
     int best = 6;
     double tbest = 1e300;
