@@ -443,7 +443,8 @@ pg_status pg_prog_plan(pg_prog prog, size_t* workspace_bytes);
  * owned by the caller and used by every later run (tape, shadows, partials).
  * Checks every gather's connectivity against its operand on the device, on the
  * null stream, and waits for it (PG_ERANGE if an entry is out of range).  For
- * gathers of 2^16 to 2^23 incidences whose sampled rows share few cache lines
+ * gathers of 2^16 to 2^23 incidences, on at most eight times as many entries,
+ * whose sampled rows share few cache lines
  * it also lists where each incidence falls in the transposed connectivity, so
  * that the reverse is stores and a sum per entry instead of atomics; runs
  * compare conn with what the list was built from, and go back to atomics for

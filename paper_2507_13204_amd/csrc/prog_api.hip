@@ -135,6 +135,13 @@ constexpr int64_t kTransposeMin = 1 << 16, kTransposeMax = 1 << 23;
 // (400,000) 80.5 and 79.6, 12 MB (10^6) 143 and 117.  And only with at most one
 // operand entry per incidence: the offsets then take no more than the products.
 constexpr int64_t kPartBytes = 6 << 20;
+// Operand entries per incidence up to which the transposed order is taken: its
+// pass reads the offsets and writes the sum of every entry, also of those that
+// no row names.  Gradients, atomics / transposed, us: 65,600 incidences on 8
+// times as many entries 20.9 / 13.9, 16 21.4 / 15.6, 100 28 / 31, 400 46 / 136;
+// 800,000 on 8 times 63 / 53, 16 70 / 85, 32 87 / 165; 1.6 M on 8 times 148 /
+// 138, 16 190 / 196, 32 256 / 326.
+constexpr int64_t kTransposeEntries = 8;
 // Incidences of one operand entry up to which one thread adds them.
 constexpr int32_t kTransposeDegree = 256;
 
@@ -655,7 +662,8 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
         if (g.gather < 0) continue;
         const Op& op = ops[(size_t)g.gather];
         const int64_t inc = op.n * op.k, nn = ops[(size_t)op.a].n;
-        if (!op.active || inc < kTransposeMin || inc > kTransposeMax) continue;
+        if (!op.active || inc < kTransposeMin || inc > kTransposeMax || nn > kTransposeEntries * inc)
+            continue;
         g.pos_off = take(sizeof(int32_t) * (size_t)inc);
         g.prod_off = take(sizeof(double) * (size_t)inc);
         g.copy_off = take(sizeof(int32_t) * (size_t)inc);
