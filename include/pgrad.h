@@ -446,9 +446,11 @@ pg_status pg_prog_plan(pg_prog prog, size_t* workspace_bytes);
  * gathers of 2^16 to 2^23 incidences, on at most eight times as many entries,
  * whose sampled rows share few cache lines
  * it also lists where each incidence falls in the transposed connectivity, so
- * that the reverse is stores and a sum per entry instead of atomics; runs
- * compare conn with what the list was built from, and go back to atomics for
- * good (until bound again) once it differs. */
+ * that the reverse is stores and a sum per entry instead of atomics (bitwise
+ * repeatable); every run compares conn with what the list was built from.
+ * Where it differs that run delivers this gather by atomics, as do the runs
+ * enqueued before it has ended and those of a graph captured before; later
+ * ones run it as a gather that did not qualify, until bound again. */
 pg_status pg_prog_bind_workspace(pg_prog prog, void* workspace, size_t bytes);
 /* inputs: host array of device pointers, one per input in creation order.
  * f_out: device FP64 (may be NULL).  grads: NULL (objective only) or a host
@@ -466,7 +468,8 @@ typedef struct {
     int32_t rev_kernels;      /* launches of the reverse pass, likewise */
     int32_t atomic_ops;       /* reverse deliveries made atomic by the race rule (gathers) */
     int32_t rescheduled_ops;  /* reverse stencils rescheduled into gathers (no atomics), and,
-                                 once bound, gathers delivered in transposed order */
+                                 once bound, gathers delivered in transposed order (until a
+                                 finished run found their connectivity changed) */
     int32_t groups;           /* fused groups of pointwise constructs (the sum's included) */
     int32_t fused_gathers;    /* gathers evaluated inside their consuming group */
     int32_t dead_ops;         /* constructs that do not feed the sum (never run) */

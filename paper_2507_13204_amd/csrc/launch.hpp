@@ -482,6 +482,7 @@ struct GatherRev {
     const double* B = nullptr;
     const double* adj = nullptr;
     const int32_t* stale = nullptr;
+    int32_t* tell = nullptr;  // if not null, host memory that is set to 1 where *stale is not 0
     double* out = nullptr;
     int accumulate = 1;
     // if f_out: the partials of f, summed into it on the way

@@ -5,6 +5,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -38,6 +39,55 @@ pg_status perr(pg_status s, const char* fmt, ...) {
 constexpr size_t kAlign = PG_WORKSPACE_ALIGN;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 constexpr size_t NONE = ~size_t(0);
+
+// Words of host memory that a kernel sets and the host looks at without
+// waiting for it: one page for the process, given out and taken back word by
+// word, allocated when the first is asked for and kept (freeing it would wait
+// for the device).  A launch still in flight when its program is destroyed may
+// set a word that another program has by then: that one's gather goes over to
+// atomics without need, which changes no result.
+class HostWords {
+public:
+    static HostWords& get() {
+        static HostWords w;
+        return w;
+    }
+    // A word holding zero, or -1 (none left, or the memory was refused).
+    int take() {
+        std::lock_guard<std::mutex> lock(mutex_);
+        if (!host_ && !refused_) {
+            void *h = nullptr, *d = nullptr;
+            refused_ = hipHostMalloc(&h, sizeof(int32_t) * kWords, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess ||
+                       hipHostGetDevicePointer(&d, h, 0) != hipSuccess;
+            if (refused_) {
+                (void)hipGetLastError();
+                return -1;
+            }
+            host_ = static_cast<int32_t*>(h);
+            device_ = static_cast<int32_t*>(d);
+        }
+        for (int i = 0; host_ && i < kWords; ++i) {
+            if (used_[i]) continue;
+            used_[i] = true;
+            __atomic_store_n(host_ + i, 0, __ATOMIC_RELAXED);
+            return i;
+        }
+        return -1;
+    }
+    void give(int i) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        used_[i] = false;
+    }
+    bool is_set(int i) const { return __atomic_load_n(host_ + i, __ATOMIC_RELAXED) != 0; }
+    int32_t* device(int i) const { return device_ + i; }
+
+private:
+    static constexpr int kWords = 1024;
+    std::mutex mutex_;
+    int32_t *host_ = nullptr, *device_ = nullptr;
+    bool refused_ = false;
+    bool used_[kWords] = {};
+};
 
 struct Op {
     int kind = P_INPUT;
@@ -81,10 +131,11 @@ struct Group {
     // (planned, when the gather is large enough), and whether it is used
     // (decided at bind from the connectivity).
     size_t pos_off = NONE, offs_off = NONE, cursor_off = NONE, copy_off = NONE, adj_off = NONE,
-           prod_off = NONE, csr_scan_off = NONE;
+           prod_off = NONE, csr_scan_off = NONE, stale_off = NONE;
     int32_t parts = 1;          // parts of the products' order (GatherRev)
     bool gather_first = false;  // its delivery is the first into the operand's shadow
     bool transposed = false;
+    int word = -1;              // host word that tells of a changed connectivity
 };
 
 // One step of the forward schedule: a non-pointwise construct or a group.
@@ -118,6 +169,14 @@ struct pg_prog_s {
     char* ws = nullptr;
     pg_prog_stats planned_stats{}, stats{};  // as planned; with what bind decided
     std::vector<char> stored_first;          // views whose first delivery turned out to store
+
+    void give_words() {
+        for (Group& g : groups) {
+            if (g.word >= 0) HostWords::get().give(g.word);
+            g.word = -1;
+        }
+    }
+    ~pg_prog_s() { give_words(); }
 };
 
 namespace {
@@ -162,6 +221,25 @@ bool scattered(const std::vector<std::vector<int32_t>>& tiles) {
     return incidences > 0 && 4 * lines >= incidences;
 }
 
+// Gathers whose connectivity a run found changed go back to atomics from the
+// first run (or query) after that one has ended.  Until then, and in a graph
+// captured before, the launches see to it on the device, which scatters without
+// combining.  Random rows of eight, then random ones again and then structured
+// ones, a gradient in transposed order / changed to random, by the device / with
+// atomics again / changed to structured, by the device / with atomics again, us:
+// 200,003 rows on 300,007 entries 38 / 104 / 121 / 40 / 16; 10^6 on 10^6 251 /
+// 562 / 421 / 182 / 34; 100,000 on 100,000 24 / 53 / 81 / 22 / 14.  (With
+// atomics from the start 125, 422 and 93 random, 15, 35 and 14 structured.)
+void settle_changed(pg_prog p) {
+    for (Group& g : p->groups) {
+        if (!g.transposed || g.word < 0 || !HostWords::get().is_set(g.word)) continue;
+        g.transposed = false;
+        p->stored_first[(size_t)p->ops[(size_t)g.gather].a] = 0;
+        ++p->stats.atomic_ops;
+        --p->stats.rescheduled_ops;
+        p->stats.rev_kernels -= 2;
+    }
+}
 
 pg_status add_view(pg_prog p, const Op& op, int32_t* view) {
     if (!p) return perr(PG_EINVAL, "program is NULL");
@@ -433,6 +511,7 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
     // member is; once a construct outside it reads a member, it is sealed
     // (it must run before that reader) and takes no further members.
     std::vector<Group>& G = p->groups;
+    p->give_words();
     G.clear();
     auto add_leaf = [&](Group& g, int32_t u) {
         if (std::find(g.leaves.begin(), g.leaves.end(), u) == g.leaves.end()) g.leaves.push_back(u);
@@ -673,6 +752,7 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
         g.cursor_off = take(sizeof(int32_t) * (size_t)runs);
         g.adj_off = take(sizeof(double) * (size_t)op.n);
         g.csr_scan_off = take(sizeof(int64_t) * (size_t)scan_scratch_items(runs));
+        g.stale_off = take(sizeof(int32_t));
     }
     p->ws_bytes = off;
 
@@ -753,7 +833,7 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
         if (op.active) p->stats.rev_kernels -= fewer;
     }
     p->stored_first.assign(p->ops.size(), 0);
-    PG_HIP(launch_zero(flag + 3, sizeof(int32_t), nullptr));  // no connectivity changed yet
+    p->give_words();
     for (Group& g : p->groups) {
         if (g.gather < 0) continue;
         const Op& op = p->ops[(size_t)g.gather];
@@ -807,6 +887,8 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
                                              reinterpret_cast<int64_t*>(w + g.csr_scan_off), nullptr));
                 PG_HIP(launch_csr_fill_sort(keys, inc, runs, offs, cursor, list, nullptr));
                 PG_HIP(launch_invert(list, inc, reinterpret_cast<int32_t*>(w + g.pos_off), nullptr));
+                PG_HIP(launch_zero(w + g.stale_off, sizeof(int32_t), nullptr));  // not changed yet
+                g.word = HostWords::get().take();
                 g.transposed = true;
                 if (g.gather_first) p->stored_first[(size_t)op.a] = 1;
                 --p->stats.atomic_ops;
@@ -843,6 +925,7 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
     hipStream_t s = static_cast<hipStream_t>(stream);
     const std::vector<Op>& ops = p->ops;
     const size_t nv = ops.size();
+    settle_changed(p);
     // Device pointers of every view's forward value and shadow.
     std::vector<const double*> val(nv, nullptr);
     std::vector<double*> shd(nv, nullptr);
@@ -935,7 +1018,7 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
                 d.gather_prod = at(p, g.prod_off);
                 d.gather_pos = reinterpret_cast<const int32_t*>(p->ws + g.pos_off);
                 d.conn_copy = reinterpret_cast<const int32_t*>(p->ws + g.copy_off);
-                d.stale = reinterpret_cast<int32_t*>(p->ws + p->flag_off) + 3;
+                d.stale = reinterpret_cast<int32_t*>(p->ws + g.stale_off);
             }
             if (g.export_gather) {
                 d.export_slot[d.n_exports] = d.gather_slot;
@@ -980,7 +1063,8 @@ pg_status pg_prog_run(pg_prog p, const double* const* inputs, double* f_out, dou
         r.conn = go.conn;
         r.B = go.B;
         r.adj = at(p, g.adj_off);
-        r.stale = reinterpret_cast<const int32_t*>(p->ws + p->flag_off) + 3;
+        r.stale = reinterpret_cast<const int32_t*>(p->ws + g.stale_off);
+        r.tell = g.word >= 0 ? HostWords::get().device(g.word) : nullptr;
         r.out = shd[(size_t)go.a];
         r.accumulate = g.gather_first ? 0 : 1;
         if (n_partials > 0 && r.n_nodes > 0) {
@@ -1038,6 +1122,7 @@ pg_status pg_prog_info(pg_prog p, pg_prog_stats* stats) {
     clear_error();
     if (!p || !stats) return perr(PG_EINVAL, "NULL argument");
     if (!p->planned) return perr(PG_ESTATE, "call pg_prog_plan first");
+    settle_changed(p);
     *stats = p->stats;
     return PG_OK;
 }

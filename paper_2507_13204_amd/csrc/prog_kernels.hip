@@ -126,7 +126,7 @@ k_part_keys(const int32_t* __restrict__ conn, int64_t n_elems, int32_t k, int64_
 }
 
 // The same by element with atomics, for a connectivity changed since the
-// transposed one was built (nothing to do otherwise).  With f_out, the first
+// transposed one was built (nothing to do otherwise), which it tells the host.  With f_out, the first
 // workgroup sums the partials of f instead, which saves that its launch.
 __global__ void __launch_bounds__(kBS) k_gather_scatter(GatherRev r) {
     __shared__ double lds[16];
@@ -137,6 +137,7 @@ __global__ void __launch_bounds__(kBS) k_gather_scatter(GatherRev r) {
         return;
     }
     if (!*r.stale) return;
+    if (r.tell && blockIdx.x == first && threadIdx.x == 0) *r.tell = 1;
     for (int64_t e = (int64_t)(blockIdx.x - first) * kBS + threadIdx.x; e < r.n_elems;
          e += (int64_t)(gridDim.x - first) * kBS) {
         const double v = r.adj[e];
