@@ -437,15 +437,17 @@ pg_status pg_prog_broadcast(pg_prog prog, int32_t a, const int64_t* offsets, int
 /* f = sum of view a.  Ends the program. */
 pg_status pg_prog_sum(pg_prog prog, int32_t a);
 /* Checks the program, runs the activity analysis, lays out the tape and the
- * shadows; *workspace_bytes (host out) is what pg_prog_bind_workspace needs. */
+ * shadows; *workspace_bytes (host out) is what pg_prog_bind_workspace needs.
+ * Looks at sampled rows of large gathers' conn (on the null stream) for whether
+ * to keep the room that the transposed order takes (see there): a conn that is
+ * filled only later may be left without. */
 pg_status pg_prog_plan(pg_prog prog, size_t* workspace_bytes);
 /* workspace: device memory of at least the planned bytes, 256-byte aligned,
  * owned by the caller and used by every later run (tape, shadows, partials).
  * Checks every gather's connectivity against its operand on the device, on the
  * null stream, and waits for it (PG_ERANGE if an entry is out of range).  For
  * gathers of 2^16 to 2^23 incidences, on at most eight times as many entries,
- * whose sampled rows share few cache lines
- * it also lists where each incidence falls in the transposed connectivity, so
+ * whose sampled rows share few cache lines it also lists where each incidence falls in the transposed connectivity, so
  * that the reverse is stores and a sum per entry instead of atomics (bitwise
  * repeatable); every run compares conn with what the list was built from.
  * Where it differs that run delivers this gather by atomics, as do the runs

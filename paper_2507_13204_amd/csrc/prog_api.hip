@@ -183,8 +183,8 @@ namespace {
 
 // Incidences of a gather from which its reverse may go through the transposed
 // connectivity (below, the extra launches cost more than the atomics), and up
-// to which the plan keeps room for it (16 bytes and a share per incidence:
-// some 150 MB).
+// to which the plan keeps room for it (16 bytes per incidence, 8 of them shared
+// by the program's gathers, and 4 to 32 per entry).
 constexpr int64_t kTransposeMin = 1 << 16, kTransposeMax = 1 << 23;
 // The products are kept in one part per XCD up to this many bytes of operand
 // and of one XCD's products, where its L2 (4 MB) holds most of both; beyond, the
@@ -204,21 +204,57 @@ constexpr int64_t kTransposeEntries = 8;
 // Incidences of one operand entry up to which one thread adds them.
 constexpr int32_t kTransposeDegree = 256;
 
-// Whether the sampled workgroups' scatter is one memory request for every
-// fourth incidence or more: a flush instruction costs a request per 128-byte
-// line of its 64 entries.
-bool scattered(const std::vector<std::vector<int32_t>>& tiles) {
+// Sampled workgroups of a gather's scatter: at most kSampled of them, evenly
+// spread.
+constexpr int64_t kSampled = 64;
+int64_t sampled_tiles(const Op& op) {
+    return std::min<int64_t>((op.n + kGroupBlockScatter - 1) / kGroupBlockScatter, kSampled);
+}
+hipError_t copy_tile(const Op& op, int64_t q, std::vector<int32_t>* out) {
+    const int64_t nt = (op.n + kGroupBlockScatter - 1) / kGroupBlockScatter, ns = sampled_tiles(op);
+    const int64_t t = nt > 1 ? q * (nt - 1) / std::max<int64_t>(ns - 1, 1) : 0;
+    const int64_t e0 = t * kGroupBlockScatter, e1 = std::min(op.n, e0 + kGroupBlockScatter);
+    out->resize((size_t)((e1 - e0) * op.k));
+    if (out->empty()) return hipSuccess;
+    return hipMemcpy(out->data(), op.conn + e0 * op.k, sizeof(int32_t) * out->size(), hipMemcpyDeviceToHost);
+}
+
+// Whether the sampled workgroups' scatter (every step-th) into n_nodes entries
+// is one memory request for every fourth incidence or more: a flush instruction
+// costs a request per 128-byte line of its 64 entries.
+bool scattered(const std::vector<std::vector<int32_t>>& tiles, size_t step, int64_t n_nodes) {
+    std::vector<uint64_t> seen((size_t)(n_nodes >> 10) + 1, 0);  // one bit per line
+    auto in = [&](int32_t n) { return n >= 0 && n < n_nodes; };  // a plan has not checked them yet
     int64_t lines = 0, incidences = 0;
-    std::vector<int32_t> l;
-    for (size_t i = 0; i < tiles.size(); i += 8) {  // every eighth: it decides more than it measures
-        const auto& t = tiles[i];
-        l.clear();
-        for (const int32_t n : t) l.push_back(n >> 4);
-        std::sort(l.begin(), l.end());
-        lines += std::unique(l.begin(), l.end()) - l.begin();
-        incidences += (int64_t)t.size();
+    for (size_t i = 0; i < tiles.size(); i += step) {
+        for (const int32_t n : tiles[i]) {
+            if (!in(n)) continue;
+            uint64_t& word = seen[(size_t)(n >> 10)];
+            const uint64_t bit = 1ull << (n >> 4 & 63);
+            lines += !(word & bit);
+            word |= bit;
+        }
+        for (const int32_t n : tiles[i])
+            if (in(n)) seen[(size_t)(n >> 10)] = 0;
+        incidences += (int64_t)tiles[i].size();
     }
     return incidences > 0 && 4 * lines >= incidences;
+}
+constexpr size_t kSampleStep = 8;  // it decides more than it measures
+
+// The same of a gather being planned, so that room is kept only for a
+// connectivity that will use it.  One that cannot be looked at (not device
+// memory) may.
+bool may_be_scattered(const Op& op, int64_t n_nodes) {
+    hipPointerAttribute_t at;
+    bool seen = hipPointerGetAttributes(&at, op.conn) == hipSuccess && at.type == hipMemoryTypeDevice;
+    std::vector<std::vector<int32_t>> tiles;
+    for (int64_t q = 0; seen && q < sampled_tiles(op); q += (int64_t)kSampleStep) {
+        tiles.emplace_back();
+        seen = copy_tile(op, q, &tiles.back()) == hipSuccess;
+    }
+    if (!seen) (void)hipGetLastError();
+    return !seen || scattered(tiles, 1, n_nodes);
 }
 
 // Gathers whose connectivity a run found changed go back to atomics from the
@@ -734,25 +770,36 @@ pg_status pg_prog_plan(pg_prog p, size_t* workspace_bytes) {
     for (const Op& op : ops)
         if (op.live && op.kind == P_SCAN) scan_chunks = std::max(scan_chunks, prog_scan_chunks(op.n));
     p->scan_off = scan_chunks ? take(sizeof(double) * (size_t)scan_chunks) : NONE;
-    // Transposed connectivity of the gathers that may be delivered through it.
+    // Transposed connectivity of the gathers that may be delivered through it;
+    // the products, adjoints and what only bind needs are one gather's at a time.
+    size_t prod_bytes = 0, rest_bytes = 0, scan_bytes = 0;
     for (Group& g : G) {
         g.transposed = false;
         g.pos_off = NONE;
         if (g.gather < 0) continue;
         const Op& op = ops[(size_t)g.gather];
         const int64_t inc = op.n * op.k, nn = ops[(size_t)op.a].n;
-        if (!op.active || inc < kTransposeMin || inc > kTransposeMax || nn > kTransposeEntries * inc)
+        if (!op.active || inc < kTransposeMin || inc > kTransposeMax || nn > kTransposeEntries * inc ||
+            !may_be_scattered(op, nn))
             continue;
         g.pos_off = take(sizeof(int32_t) * (size_t)inc);
-        g.prod_off = take(sizeof(double) * (size_t)inc);
         g.copy_off = take(sizeof(int32_t) * (size_t)inc);
         g.parts = nn <= inc && 8 * nn + inc <= kPartBytes ? kXcds : 1;
         const int64_t runs = nn * g.parts;
         g.offs_off = take(sizeof(int32_t) * (size_t)(runs + 1));
-        g.cursor_off = take(sizeof(int32_t) * (size_t)runs);
-        g.adj_off = take(sizeof(double) * (size_t)op.n);
-        g.csr_scan_off = take(sizeof(int64_t) * (size_t)scan_scratch_items(runs));
         g.stale_off = take(sizeof(int32_t));
+        prod_bytes = std::max(prod_bytes, sizeof(double) * (size_t)inc);
+        rest_bytes = std::max(rest_bytes, std::max(sizeof(double) * (size_t)op.n, sizeof(int32_t) * (size_t)runs));
+        scan_bytes = std::max(scan_bytes, sizeof(int64_t) * (size_t)scan_scratch_items(runs));
+    }
+    if (prod_bytes) {
+        const size_t prod = take(prod_bytes), rest = take(rest_bytes), scan = take(scan_bytes);
+        for (Group& g : G) {
+            if (g.pos_off == NONE) continue;
+            g.prod_off = prod;
+            g.adj_off = g.cursor_off = rest;
+            g.csr_scan_off = scan;
+        }
     }
     p->ws_bytes = off;
 
@@ -837,26 +884,12 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
     for (Group& g : p->groups) {
         if (g.gather < 0) continue;
         const Op& op = p->ops[(size_t)g.gather];
-        const int64_t span = kGroupBlockScatter, nt = (op.n + span - 1) / span;
-        const int64_t ns = std::min<int64_t>(nt, 64);
-        std::vector<std::vector<int32_t>> tiles;
-        for (int64_t q = 0; q < ns; ++q) {
-            const int64_t t = nt > 1 ? q * (nt - 1) / std::max<int64_t>(ns - 1, 1) : 0;
-            const int64_t e0 = t * span, e1 = std::min(op.n, e0 + span);
-            tiles.emplace_back((size_t)((e1 - e0) * op.k));
-            if (tiles.back().empty()) continue;
-            PG_HIP(hipMemcpy(tiles.back().data(), op.conn + e0 * op.k,
-                             sizeof(int32_t) * tiles.back().size(), hipMemcpyDeviceToHost));
-        }
-        std::vector<const int32_t*> ptr;
-        std::vector<int64_t> cnt;
-        for (const auto& t : tiles) {
-            ptr.push_back(t.data());
-            cnt.push_back((int64_t)t.size());
-        }
+        std::vector<std::vector<int32_t>> tiles((size_t)sampled_tiles(op));
         if (tiles.empty()) continue;
         g.transposed = false;
-        if (g.pos_off != NONE && scattered(tiles)) {
+        if (g.pos_off != NONE)
+            for (size_t q = 0; q < tiles.size(); q += kSampleStep) PG_HIP(copy_tile(op, (int64_t)q, &tiles[q]));
+        if (g.pos_off != NONE && scattered(tiles, kSampleStep, p->ops[(size_t)op.a].n)) {
             const int64_t inc = op.n * op.k, nn = p->ops[(size_t)op.a].n;
             char* w = static_cast<char*>(ws);
             int32_t* cursor = reinterpret_cast<int32_t*>(w + g.cursor_off);
@@ -897,11 +930,18 @@ pg_status pg_prog_bind_workspace(pg_prog p, void* ws, size_t bytes) {
                 continue;
             }
         }
+        std::vector<const int32_t*> ptr;
+        std::vector<int64_t> cnt;
+        for (size_t q = 0; q < tiles.size(); ++q) {
+            if (tiles[q].empty()) PG_HIP(copy_tile(op, (int64_t)q, &tiles[q]));
+            ptr.push_back(tiles[q].data());
+            cnt.push_back((int64_t)tiles[q].size());
+        }
         choose_table(ptr.data(), cnt.data(), (int64_t)tiles.size(), &g.agg_slots, &g.hash_shift);
         // The smaller table only if no workgroup of the gather would probe in it.
         if (g.agg_slots == 2048) {
             PG_HIP(launch_zero(flag + 2, sizeof(int32_t), nullptr));
-            PG_HIP(launch_table_check(op.conn, op.n, op.k, span, g.hash_shift, 2048, flag + 2, nullptr));
+            PG_HIP(launch_table_check(op.conn, op.n, op.k, kGroupBlockScatter, g.hash_shift, 2048, flag + 2, nullptr));
             int32_t miss = 0;
             PG_HIP(hipMemcpy(&miss, flag + 2, sizeof miss, hipMemcpyDeviceToHost));
             if (miss) {

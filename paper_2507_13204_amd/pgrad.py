@@ -708,6 +708,8 @@ class Program:
         check(lib().pg_prog_sum(self._p, int(a)), "pg_prog_sum")
 
     def plan(self, device="cuda") -> "Program":
+        if self._keep:
+            torch.cuda.synchronize(device)  # operands are complete before they are looked at
         sz = ctypes.c_size_t()
         check(lib().pg_prog_plan(self._p, ctypes.byref(sz)), "pg_prog_plan")
         self.workspace_bytes = sz.value
@@ -715,7 +717,6 @@ class Program:
         off = (-raw.data_ptr()) % WORKSPACE_ALIGN
         self._ws_raw = raw
         self._ws = raw[off:off + sz.value]
-        torch.cuda.synchronize(device)  # operands are complete before the connectivity check
         check(lib().pg_prog_bind_workspace(self._p, ctypes.c_void_p(self._ws.data_ptr()),
                                            sz.value), "pg_prog_bind_workspace")
         return self

@@ -88,3 +88,25 @@ def test_changed_connectivity_takes_its_gather_alone_to_the_atomics():
     assert prog.info() == before
     f, (g,) = prog.run([xd])
     check(f, g)
+
+
+def test_room_is_kept_only_where_it_is_used():
+    """A structured connectivity reserves nothing for the transposed order;
+    two gathers share what one of them uses at a time."""
+    from paper_2507_13204_amd import Program
+    n, E, k = 40_011, 40_011, 4
+    x, spec = _gather(n, E, k, 5)
+    one = Program.from_spec(spec).plan("cuda")
+    local = list(spec)
+    local[1] = ("gather", 0, ((np.arange(E)[:, None] + np.arange(k)) % n).astype(np.int32), spec[1][3])
+    prog = Program.from_spec(local).plan("cuda")
+    assert prog.workspace_bytes < 8 * n + (1 << 16) < one.workspace_bytes
+    _check(prog, local, x)
+    two = spec[:4] + [("mul", 2, 3), ("gather", 0, np.roll(spec[1][2], 1, axis=1), spec[1][3]),
+                      ("map", 5, "square"), ("add", 4, 1.0, 6, 0.5), ("sum", 7)]
+    prog = Program.from_spec(two).plan("cuda")
+    assert prog.info()["atomic_ops"] == 0
+    # of its own: places, rows and (in eight parts) offsets; the group that adds
+    # the two keeps one gathered value and its shadow
+    assert prog.workspace_bytes - one.workspace_bytes <= 8 * E * k + 32 * (n + 1) + 16 * E + 4096
+    _check(prog, two, x)
