@@ -139,9 +139,13 @@ __device__ __forceinline__ double final_sum_block(const double* __restrict__ p, 
     return r;
 }
 
-// Takes the ticket; true for the last of n.
+// Takes the ticket; true for the last of n, which leaves it at zero for the next
+// launch.  The count wraps by itself: launches of n that overlap by mistake may
+// mix up their sums, but n tickets each later it is at zero again (reset by the
+// last one's store, it kept what others took in between, and no later launch
+// of the plan found its last workgroup right).
 __device__ __forceinline__ bool take_ticket(int32_t* ticket, int n) {
-    return __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    return atomicInc(reinterpret_cast<unsigned*>(ticket), (unsigned)n - 1) == (unsigned)n - 1;
 }
 
 template <typename T>

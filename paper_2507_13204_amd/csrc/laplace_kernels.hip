@@ -84,10 +84,7 @@ k_laplace1d(int64_t n, const T* __restrict__ x, const T* __restrict__ b, double*
             for (int q = threadIdx.x; q < (int)gridDim.x; q += blockDim.x)
                 v += read_published(partials + q);
             v = block_sum<256>(v, lds);
-            if (threadIdx.x == 0) {
-                if (f_out) f_out[0] = v;
-                *ticket = 0;
-            }
+            if (threadIdx.x == 0 && f_out) f_out[0] = v;
         }
     }
 }

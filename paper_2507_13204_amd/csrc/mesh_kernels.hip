@@ -34,10 +34,7 @@ __device__ __forceinline__ void sum_by_ticket(const MeshPass& p, uint32_t lb, do
     __syncthreads();
     if (last) {
         const double f = final_sum_block<true>(p.partials, gridDim.x, lds);
-        if (threadIdx.x == 0) {
-            p.f_out[0] = f;
-            *p.ticket = 0;
-        }
+        if (threadIdx.x == 0) p.f_out[0] = f;
     }
 }
 

@@ -480,10 +480,7 @@ __device__ __forceinline__ void sum_by_last(const GroupDev& g, double* lds, int*
         double v = 0.0;
         for (int q = threadIdx.x; q < (int)gridDim.x; q += BS) v += read_published(g.partials + q);
         v = block_sum<BS>(v, lds);
-        if (threadIdx.x == 0) {
-            *g.f_out = v;
-            *g.ticket = 0;
-        }
+        if (threadIdx.x == 0) *g.f_out = v;
     }
 }
 
