@@ -43,14 +43,32 @@ void check(PyObject* py_check, int status, const char* where) {
     throw python_error();
 }
 
+// What the binding checks of every operand: a hook may hand back another
+// tensor than the one that was saved or passed on.
+bool operand(const Tensor& t) { return t.is_cuda() && t.is_contiguous(); }
+// Raises as the binding does for operands that are not (any thread).
+[[noreturn]] void refuse(PyObject* py_check, const char* fn, const Tensor& a, const Tensor& b) {
+    pybind11::gil_scoped_acquire gil;
+    try {
+        pybind11::dict binding = pybind11::handle(py_check).attr("__globals__");
+        binding[fn](a);
+        binding[fn](b);
+        binding["check"]((int)PG_EINVAL, "backward");  // it found nothing: still not to be used
+    } catch (pybind11::error_already_set& e) {
+        e.restore();
+    }
+    throw python_error();
+}
+
 enum Policy { GRADIENT = 0, STORE = 1 };
 
 struct ObjectiveNode : public torch::autograd::Node {
     std::string label;
     int policy = GRADIENT;
     SavedVariable first, second;  // the gradient; or the tape and x
-    std::vector<int64_t> f_sizes;
-    c10::TensorOptions f_options;
+    std::vector<int64_t> f_sizes, x_sizes;
+    c10::TensorOptions f_options, x_options;
+    int64_t tape_bytes = 0;
     PyObject* obj = nullptr;  // owns the plan
     PyObject* py_check = nullptr;
 
@@ -70,14 +88,18 @@ struct ObjectiveNode : public torch::autograd::Node {
     variable_list apply(variable_list&& grads) override {
         std::lock_guard<std::mutex> lock(mutex_);
         const Tensor a = first.unpack();
-        Tensor x;
-        if (policy == STORE) x = second.unpack();
+        if (policy == STORE) second.unpack();  // for its checks; only its shape is needed
         at::AutoDispatchBelowADInplaceOrView below;
         Tensor seed = grads[0].defined() ? grads[0] : at::zeros(f_sizes, f_options);
         if (seed.scalar_type() != at::kDouble) seed = seed.to(at::kDouble);
         seed = seed.contiguous();
+        const bool enough = seed.numel() >= c10::multiply_integers(f_sizes) &&
+                            (policy == GRADIENT || (int64_t)a.nbytes() >= tape_bytes);
+        if (!operand(seed) || !operand(a) || !enough) refuse(py_check, "_need_cuda", seed, a);
         const double* fbar = seed.const_data_ptr<double>();
         if (policy == GRADIENT) {
+            if (a.scalar_type() != at::kDouble && a.scalar_type() != at::kFloat)
+                refuse(py_check, "_dtype_code", a, a);
             Tensor y = at::empty_like(a);
             check(py_check,
                   pg_scale(a.scalar_type() == at::kDouble ? PG_F64 : PG_F32, a.numel(), fbar,
@@ -85,7 +107,7 @@ struct ObjectiveNode : public torch::autograd::Node {
                   "pg_scale");
             return {y};
         }
-        Tensor y = at::empty_like(x);
+        Tensor y = at::empty(x_sizes, x_options);
         check(py_check,
               pg_adjoint_tape(plan_of(obj), fbar, a.const_data_ptr(), y.mutable_data_ptr(),
                               current_stream()),
@@ -135,6 +157,9 @@ pybind11::object apply(const Tensor& x, pybind11::object obj, uintptr_t plan, in
         at::AutoDispatchBelowADInplaceOrView below;
         xc = x.contiguous();
         node->f_options = x.options().dtype(at::kDouble);
+        node->x_options = x.options();
+        node->x_sizes = x.sizes().vec();
+        node->tape_bytes = 8 * tape_doubles;
         if (n_f >= 0) node->f_sizes.push_back(n_f);
         f = at::empty(node->f_sizes, node->f_options);
         pg_plan p = reinterpret_cast<pg_plan>(plan);
