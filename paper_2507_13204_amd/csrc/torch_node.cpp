@@ -18,6 +18,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/autograd/variable.h>
 #include <torch/csrc/Exceptions.h>
@@ -63,7 +64,6 @@ bool operand(const Tensor& t) { return t.is_cuda() && t.is_contiguous(); }
 enum Policy { GRADIENT = 0, STORE = 1 };
 
 struct ObjectiveNode : public torch::autograd::Node {
-    std::string label;
     int policy = GRADIENT;
     SavedVariable first, second;  // the gradient; or the tape and x
     std::vector<int64_t> f_sizes, x_sizes;
@@ -78,7 +78,13 @@ struct ObjectiveNode : public torch::autograd::Node {
         Py_XDECREF(obj);
         Py_XDECREF(py_check);
     }
-    std::string name() const override { return label; }
+    // What was saved, as the Function's context gives it.
+    variable_list saved() {
+        std::lock_guard<std::mutex> lock(mutex_);
+        variable_list v{first.unpack()};
+        if (policy == STORE) v.push_back(second.unpack());
+        return v;
+    }
     void release_variables() override {
         std::lock_guard<std::mutex> lock(mutex_);
         first.reset_data();
@@ -123,6 +129,73 @@ struct ObjectiveNode : public torch::autograd::Node {
     }
 };
 
+// One node class, and Python type of f.grad_fn, per Function.
+constexpr const char* kLabels[] = {"MeshFnBackward", "DenseFnBackward", "BatchedDenseFnBackward",
+                                   "MeshBatchFnBackward"};
+constexpr int kNLabels = 4;
+template <int L>
+struct LabelledNode final : ObjectiveNode {
+    std::string name() const override { return kLabels[L]; }
+};
+
+std::shared_ptr<ObjectiveNode> new_node(int label) {
+    ObjectiveNode* n = label == 0   ? (ObjectiveNode*)new LabelledNode<0>()
+                       : label == 1 ? (ObjectiveNode*)new LabelledNode<1>()
+                       : label == 2 ? (ObjectiveNode*)new LabelledNode<2>()
+                                    : (ObjectiveNode*)new LabelledNode<3>();
+    return std::shared_ptr<ObjectiveNode>(n, torch::autograd::deleteNode);
+}
+
+// The attributes of the Function's context that f.grad_fn had.
+ObjectiveNode& node_of(PyObject* self) {
+    return static_cast<ObjectiveNode&>(*reinterpret_cast<torch::autograd::THPCppFunction*>(self)->cdata);
+}
+PyObject* get_saved_tensors(PyObject* self, void*) {
+    HANDLE_TH_ERRORS
+    variable_list v;
+    {
+        pybind11::gil_scoped_release off;  // the engine may hold the node while a hook waits for this
+        v = node_of(self).saved();
+    }
+    pybind11::tuple t(v.size());
+    for (size_t i = 0; i < v.size(); ++i) t[i] = pybind11::cast(v[i]);
+    return t.release().ptr();
+    END_HANDLE_TH_ERRORS
+}
+PyObject* get_needs_input_grad(PyObject*, void*) { return Py_BuildValue("(OOO)", Py_True, Py_False, Py_False); }
+PyObject* get_obj(PyObject* self, void*) {
+    PyObject* o = node_of(self).obj;
+    Py_INCREF(o);
+    return o;
+}
+PyObject* get_policy(PyObject* self, void*) {
+    return PyUnicode_FromString(node_of(self).policy == STORE ? "store" : "gradient");
+}
+
+template <int L>
+void register_type() {
+    using namespace torch::autograd;
+    static PyMethodDef methods[] = {{"_register_hook_dict", THPCppFunction_register_hook_dict, METH_O, nullptr},
+                                    {"register_hook", THPCppFunction_register_hook, METH_O, nullptr},
+                                    {"register_prehook", THPCppFunction_register_prehook, METH_O, nullptr},
+                                    {"name", THPCppFunction_name, METH_NOARGS, nullptr},
+                                    {"_sequence_nr", THPCppFunction_sequence_nr, METH_NOARGS, nullptr},
+                                    {nullptr, nullptr, 0, nullptr}};
+    static PyGetSetDef properties[] = {
+        {"next_functions", THPCppFunction_next_functions, nullptr, nullptr, nullptr},
+        {"requires_grad", THPCppFunction_requires_grad, nullptr, nullptr, nullptr},
+        {"metadata", THPCppFunction_metadata, nullptr, nullptr, nullptr},
+        {"_input_metadata", THPCppFunction_input_metadata, nullptr, nullptr, nullptr},
+        {"saved_tensors", get_saved_tensors, nullptr, nullptr, nullptr},
+        {"needs_input_grad", get_needs_input_grad, nullptr, nullptr, nullptr},
+        {"obj", get_obj, nullptr, nullptr, nullptr},
+        {"policy", get_policy, nullptr, nullptr, nullptr},
+        {nullptr, nullptr, nullptr, nullptr, nullptr}};
+    static PyTypeObject type{};
+    torch::autograd::_initFunctionPyTypeObject(type, kLabels[L], properties, methods);
+    torch::autograd::registerCppFunction(typeid(LabelledNode<L>), &type);
+}
+
 // A launch may wait for the device's queue: other threads go on meanwhile.
 template <class F>
 int unlocked(F&& call) {
@@ -145,13 +218,13 @@ bool plain(const Tensor& x) {
 }
 
 // f of x with its node, or None where the Python Function has to take over.
-// plan, policy and label are the objective's and the Function's; n_f is the
+// plan, policy and label (of kLabels) are the objective's and the Function's; n_f is the
 // number of objectives (-1: a scalar); tape_doubles the tape's size.
 pybind11::object apply(const Tensor& x, pybind11::object obj, uintptr_t plan, int policy,
-                       int64_t n_f, int64_t tape_doubles, const char* label,
+                       int64_t n_f, int64_t tape_doubles, int label,
                        pybind11::object py_check) {
-    if (plan == 0 || !plain(x)) return pybind11::none();
-    auto node = std::shared_ptr<ObjectiveNode>(new ObjectiveNode(), torch::autograd::deleteNode);
+    if (plan == 0 || label < 0 || label >= kNLabels || !plain(x)) return pybind11::none();
+    auto node = new_node(label);
     Tensor f, a, xc;
     {
         at::AutoDispatchBelowADInplaceOrView below;
@@ -179,7 +252,6 @@ pybind11::object apply(const Tensor& x, pybind11::object obj, uintptr_t plan, in
                   "pg_objective_tape");
         }
     }
-    node->label = label;
     node->policy = policy;
     node->obj = obj.release().ptr();
     node->py_check = py_check.release().ptr();
@@ -192,4 +264,10 @@ pybind11::object apply(const Tensor& x, pybind11::object obj, uintptr_t plan, in
 
 }  // namespace
 
-PYBIND11_MODULE(_pgrad_torch, m) { m.def("apply", &apply); }
+PYBIND11_MODULE(_pgrad_torch, m) {
+    register_type<0>();
+    register_type<1>();
+    register_type<2>();
+    register_type<3>();
+    m.def("apply", &apply);
+}

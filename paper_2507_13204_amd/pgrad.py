@@ -891,7 +891,7 @@ class MeshBatchFn(_ObjectiveFn):
 _PLAIN_TENSORS = (torch.Tensor, torch.nn.Parameter)
 _NODE_OBJECTIVES = (MeshObjective, DenseObjective, BatchedDense, MeshBatch)
 _NODE_POLICIES = {"gradient": 0, "store": 1}
-_NODE_LABELS = {c: c.__name__ + "Backward" for c in (MeshFn, DenseFn, BatchedDenseFn, MeshBatchFn)}
+_NODE_LABELS = {c: i for i, c in enumerate((MeshFn, DenseFn, BatchedDenseFn, MeshBatchFn))}  # kLabels
 _node_module = None
 
 

@@ -91,3 +91,35 @@ def test_an_error_of_the_forward_is_the_bindings(policy):
             fn.apply(empty, obj)
     _fns()[0].apply(x, obj).backward()
     assert torch.isfinite(x.grad).all()
+
+
+def test_grad_fn_has_the_contexts_attributes():
+    """What a caller could read of the Function's context through f.grad_fn."""
+    import gc
+    import weakref
+    from paper_2507_13204_amd import DenseFn, DenseObjective
+    for policy in ("gradient", "store"):
+        obj, x = _mesh(policy)
+        for fn in _fns():
+            f = fn.apply(x, obj)
+            ctx = f.grad_fn
+            assert ctx.obj is obj and ctx.policy == policy and ctx.needs_input_grad == (True, False, False)
+            saved = ctx.saved_tensors
+            assert [t.shape for t in saved][-1] == x.shape and len(saved) == (2 if policy == "store" else 1)
+            assert ctx.next_functions[0][0].name() == "torch::autograd::AccumulateGrad"
+            f.backward()
+            if policy == "gradient":
+                assert torch.equal(x.grad, saved[0])
+            with pytest.raises(RuntimeError, match="second time"):
+                ctx.saved_tensors
+            x.grad = None
+    f = _fns()[0].apply(x, obj)
+    assert f.grad_fn is f.grad_fn and f.grad_fn.name() == type(f.grad_fn).__name__ == "MeshFnBackward"
+    A = torch.ones(3, 4, dtype=torch.float64, device="cuda")
+    d = DenseObjective(A, torch.ones(3, dtype=torch.float64, device="cuda"))
+    y = torch.ones(4, dtype=torch.float64, device="cuda", requires_grad=True)
+    assert type(DenseFn.apply(y, d).grad_fn).__name__ == "DenseFnBackward"
+    ref = weakref.ref(obj)  # reading the attributes keeps nothing
+    del f, obj, ctx, saved
+    gc.collect()
+    assert ref() is None
