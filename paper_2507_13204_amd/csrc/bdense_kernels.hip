@@ -584,9 +584,10 @@ Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SP
 // takes a shape within 6% of the best one at 12 FP64 sizes from 300 x 300 to
 // 4,096 x 1,024 (5,000 x 17 and 6,000 x 33 among them), within 8% at 15 split
 // ones from 1,024 x 1,024 to 8,000 x 140 and 6,000 x 1,000, and within 12% at
-// 11 of the FP32 instruction.
+// 11 of the FP32 instruction, whose fewer than 2^20 entries are never faster in
+// the two largest tiles.
 constexpr ShapeInfo kShapes[] = {
-    info<S0>(7.7, 5.8, 3.95),  info<S1>(7.8, 5.8, 4.25),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.1),
+    info<S0>(7.7, 1e9, 3.95),  info<S1>(7.8, 1e9, 4.25),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.1),
     info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 9.0), info<S6>(22.7, 11.0, 11.0),
     info<S7>(1e9, 1e9, 4.5)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
@@ -639,8 +640,14 @@ hipError_t launch_gemm(const BDenseView& b, hipStream_t s, const T* A, const T* 
                        double* partials, T* V, const double* fbar, T* G, int accumulate, int64_t np,
                        double* f_out) {
     switch (b.shape) {
-        case 0: return launch_shape<T, AR, TRANS, EPI, S0>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
-        case 1: return launch_shape<T, AR, TRANS, EPI, S1>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 0:
+            if constexpr (AR != FP32)
+                return launch_shape<T, AR, TRANS, EPI, S0>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+            break;
+        case 1:
+            if constexpr (AR != FP32)
+                return launch_shape<T, AR, TRANS, EPI, S1>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+            break;
         case 2: return launch_shape<T, AR, TRANS, EPI, S2>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 3: return launch_shape<T, AR, TRANS, EPI, S3>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 4: return launch_shape<T, AR, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);

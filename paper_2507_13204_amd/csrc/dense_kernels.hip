@@ -568,11 +568,15 @@ hipError_t launch_fused_vn(const DenseView& d, int nw, const T* x, const double*
         PG_Q(8, 5) PG_Q(8, 6) PG_Q(8, 8) PG_Q(8, 10) PG_Q(8, 12) PG_Q(8, 16) PG_Q(8, 20)
         PG_Q(8, 24) PG_Q(8, 32)
     } else {
+        // With two elements to a slice, a row too long for fewer waves takes
+        // two slices of four waves at least, three of eight.
         PG_Q(1, 1) PG_Q(1, 2)
         if constexpr (VN == 2) { PG_Q(1, 3) PG_Q(1, 4) }
-        PG_Q(4, 1) PG_Q(4, 2)
+        if constexpr (VN == 4) { PG_Q(4, 1) }
+        PG_Q(4, 2)
         if constexpr (VN == 2) { PG_Q(4, 3) PG_Q(4, 4) }
-        PG_Q(8, 2) PG_Q(8, 3) PG_Q(8, 4) PG_Q(8, 5) PG_Q(8, 6) PG_Q(8, 8) PG_Q(8, 10) PG_Q(8, 12)
+        if constexpr (VN == 4) { PG_Q(8, 2) }
+        PG_Q(8, 3) PG_Q(8, 4) PG_Q(8, 5) PG_Q(8, 6) PG_Q(8, 8) PG_Q(8, 10) PG_Q(8, 12)
         PG_Q(8, 16)
     }
 #undef PG_Q
