@@ -550,7 +550,7 @@ k_gemm_mfma(const T* __restrict__ A, const T* __restrict__ Bm, int64_t M, int64_
 }
 
 // A workgroup has eight waves in every shape; they share a tile by splitting
-// it or the contraction.  Large tiles move the fewest operand bytes, small
+// it or the contraction (not one of a step or two: 16 x 256).  Large tiles move the fewest operand bytes, small
 // ones fill the device when C is small.  Two workgroups per compute unit (four
 // waves per SIMD) with one k-step in flight beat one with two or three for the
 // middle shapes (3,000 x 500, FP64 / FP32: 64 x 32 341 / 255 -> 334 / 230 us,
@@ -563,33 +563,41 @@ using S4 = Shape<2, 2, 1, 1, 8, 1, 1, 4>;  // 32 x 32
 using S5 = Shape<2, 1, 1, 1, 8, 3, 2, 2>;  // 32 x 16
 using S6 = Shape<1, 1, 1, 1, 8, 4, 2, 2>;  // 16 x 16, the one that takes any size
 using S7 = Shape<3, 2, 1, 4, 2, 2, 1, 2>;  // 48 x 128, split FP32 operands only
+using S8 = Shape<1, 2, 1, 8, 1, 1, 1, 4>;  // 16 x 256, for contractions too short to share
 struct ShapeInfo {
     int tm, tn, bx, by;
-    double cost[3];  // by Arith
+    double cost[3], entry[3];  // by Arith
 };
 template <typename S>
-constexpr ShapeInfo info(double c64, double c32, double split) {
-    return {S::TM, S::TN, S::BX, S::BY, {c64, c32, split}};
+constexpr ShapeInfo info(double c64, double c32, double split, double e64, double e32, double esplit) {
+    return {S::TM, S::TN, S::BX, S::BY, {c64, c32, split}, {e64, e32, esplit}};
 }
+constexpr double kNever = 1e9;  // not built
 
-// Whether FP32 operands are split.  Gradients, FP32 instruction / split, us:
-// 300 x 300 13.5 / 17.7, 512 x 512 20.6 / 19.7, 700 x 700 37.4 / 43.2, 900 x
-// 900 79 / 65, 1,000 x 1,000 102 / 73, 2,000 x 540 217 / 131, 10,000 x 100 1,091
-// / 593.  From 2^20 entries the split is the faster one at every shape tried;
-// below, either may be, and the products keep the FP32 instruction's bits.
-bool splits(const BDenseView& b) { return b.dtype == F32 && b.m * b.n >= (1 << 20); }
+// Whether FP32 operands are split.  Gradients, FP32 instruction / split, us, each
+// in its best shape: 300 x 300 13.5 / 17.7, 512 x 512 20.6 / 19.7, 700 x 700 37.4
+// / 43.2, 900 x 900 79 / 65, 1,000 x 1,000 95 / 73, 2,000 x 540 217 / 131, 10,000 x
+// 100 1,091 / 593; of few rows, 16 x 100,000 21 / 26, 48 x 100,000 52 / 82, 130 x
+// 100,000 200 / 230, 200 x 20,000 117 / 118, 300 x 20,000 177 / 161, 500 x 20,000
+// 376 / 302.  From 2^20 entries and 256 rows the split is the faster one at
+// every shape tried; below, either may be, and the products keep the FP32
+// instruction's bits.
+bool splits(const BDenseView& b) { return b.dtype == F32 && b.m >= 256 && b.m * b.n >= (1 << 20); }
 Arith arith(const BDenseView& b) { return b.dtype == F64 ? FP64 : splits(b) ? SPLIT : FP32; }
-// cost: picoseconds per product and entry of a tile with every compute unit
-// busy, from whole gradients at 4,096 x 1,024 and 3,000 x 500.  The rule below
-// takes a shape within 6% of the best one at 12 FP64 sizes from 300 x 300 to
-// 4,096 x 1,024 (5,000 x 17 and 6,000 x 33 among them), within 8% at 15 split
-// ones from 1,024 x 1,024 to 8,000 x 140 and 6,000 x 1,000, and within 12% at
-// 11 of the FP32 instruction, whose fewer than 2^20 entries are never faster in
-// the two largest tiles.
+// cost, entry: picoseconds per product and, besides, per entry of a tile with
+// every compute unit busy, fitted to whole gradients at 152 sizes from 1 x 1,000
+// to 8,000 x 140 and 4,096 x 1,024 in every shape.  The rule below takes the
+// best shape or one within 17% of it there, 1.2% on average.  (By the products
+// alone it was 22% on average and a factor of nine where a short contraction
+// meets many columns: 16 x 100,000, FP64 / FP32, 105 / 38 us in 16 x 16 tiles
+// with eight waves to share 16 products, 24 / 21 in 16 x 256.)  kNever: a form
+// that the rule takes at no size (gone through for m up to 270,000, n to 2e8).
 constexpr ShapeInfo kShapes[] = {
-    info<S0>(7.7, 1e9, 3.95),  info<S1>(7.8, 1e9, 4.25),  info<S2>(9.1, 6.9, 5.5), info<S3>(9.1, 7.1, 6.1),
-    info<S4>(10.0, 7.4, 6.6), info<S5>(16.0, 10.0, 9.0), info<S6>(22.7, 11.0, 11.0),
-    info<S7>(1e9, 1e9, 4.5)};
+    info<S0>(7.7, kNever, 3.8, 1600, 0, 1600),     info<S1>(7.6, kNever, 3.85, 2600, 0, 3000),
+    info<S2>(8.3, 9.0, 5.1, 1900, 1900, 2500),     info<S3>(8.2, 8.8, 5.3, 2500, 2100, 3700),
+    info<S4>(8.5, 8.5, 5.6, 3900, 3200, 6200),     info<S5>(14.4, 14.2, 8.6, 7800, 3500, 15500),
+    info<S6>(19.8, 14.1, kNever, 15500, 4300, 0),  info<S7>(kNever, kNever, 4.15, 0, 0, 3650),
+    info<S8>(14.8, 11.5, 7.5, 1400, 1300, 2200)};
 constexpr int kNShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
 int64_t tiles_of(const BDenseView& b, int sh) {
@@ -611,7 +619,8 @@ int bdense_shape(const BDenseView& b) {
     for (int i = 0; i < kNShapes; ++i) {
         const ShapeInfo& s = kShapes[i];
         if ((s.bx > 1 && b.m < 16 * s.bx) || (s.by > 1 && b.n < 16 * s.by)) continue;
-        const double t = (double)((tiles_of(b, i) + 255) / 256) * s.tm * s.tn * s.cost[arith(b)];
+        const double t = (double)((tiles_of(b, i) + 255) / 256) * s.tm * s.tn *
+                         (2.0 * (double)b.m * s.cost[arith(b)] + s.entry[arith(b)]);
         if (t < tbest) {
             tbest = t;
             best = i;
@@ -652,10 +661,15 @@ hipError_t launch_gemm(const BDenseView& b, hipStream_t s, const T* A, const T* 
         case 3: return launch_shape<T, AR, TRANS, EPI, S3>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 4: return launch_shape<T, AR, TRANS, EPI, S4>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
         case 5: return launch_shape<T, AR, TRANS, EPI, S5>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
-        case 6: return launch_shape<T, AR, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+        case 6:
+            if constexpr (AR != SPLIT)
+                return launch_shape<T, AR, TRANS, EPI, S6>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+            break;
         case 7:
             if constexpr (AR == SPLIT)
                 return launch_shape<T, AR, TRANS, EPI, S7>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
+            break;
+        case 8: return launch_shape<T, AR, TRANS, EPI, S8>(b, s, A, Bm, W, partials, V, fbar, G, accumulate, np, f_out);
     }
     return hipErrorInvalidValue;
 }
