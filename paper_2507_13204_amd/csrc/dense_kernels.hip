@@ -408,8 +408,9 @@ k_dense_colsum(const double* __restrict__ colpart, int nbands, int64_t cols, T* 
 
 // Pass over rows of any length: a workgroup takes U rows at a time (they
 // share the loads of x), rows dealt round-robin; f's share per workgroup
-// and, when v != nullptr, v_i = fbar w_i psi'(r_i).
-template <typename T, int VN, int U, int BS>
+// and, when v != nullptr, v_i = fbar w_i psi'(r_i).  XA: x is aligned to the
+// slices that the rows are read in, else it is read by element.
+template <typename T, int VN, int U, int BS, bool XA>
 __global__ void __launch_bounds__(BS)
 k_dense_rows(DenseView d, const T* __restrict__ x, const double* __restrict__ fbar,
              double* __restrict__ partials, double* __restrict__ v) {
@@ -424,7 +425,13 @@ k_dense_rows(DenseView d, const T* __restrict__ x, const double* __restrict__ fb
     const int64_t cols = d.cols, nvec = cols / VN;  // VN divides cols
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     const double fb = fbar ? fbar[0] : 1.0;
-    const SV* __restrict__ xv = reinterpret_cast<const SV*>(x);
+    auto load_x = [&](int64_t j) {
+        if constexpr (XA) return reinterpret_cast<const SV*>(x)[j];
+        SV r;
+#pragma unroll
+        for (int c = 0; c < VN; ++c) r.v[c] = x[j * VN + c];
+        return r;
+    };
     double tsum = 0.0;
     int phase = 0;
     for (int64_t i0 = (int64_t)blockIdx.x * U; i0 < d.rows; i0 += (int64_t)gridDim.x * U) {
@@ -440,7 +447,7 @@ k_dense_rows(DenseView d, const T* __restrict__ x, const double* __restrict__ fb
         for (; j + (D - 1) * BS < nvec; j += D * BS) {
             SV xs[D], a[U][D];
 #pragma unroll
-            for (int q = 0; q < D; ++q) xs[q] = xv[j + q * BS];
+            for (int q = 0; q < D; ++q) xs[q] = load_x(j + q * BS);
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -454,7 +461,7 @@ k_dense_rows(DenseView d, const T* __restrict__ x, const double* __restrict__ fb
                         dot[u] += to_f64(a[u][q].v[c]) * to_f64(xs[q].v[c]);
         }
         for (; j < nvec; j += BS) {
-            const SV xs = xv[j];
+            const SV xs = load_x(j);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const SV a = row[u][j];
@@ -621,17 +628,34 @@ hipError_t launch_fused_t(const DenseView& d, const DenseCfg& c, const void* x, 
                : launch_fused_vn<T, 1>(d, c.nw, xp, fbar, want_grad, partials, colpart, c.bands, s);
 }
 
-template <typename T, int VN>
+// Rows a workgroup of the row pass takes at a time, and its threads.  Many rows:
+// four at a time, which share the loads of x.  Fewer than 1,024: one, so that
+// more of the device reads; a wide workgroup each for very few very long ones
+// (more than 48 slices for each of 256 threads).
+// Objectives, us, FP64 / FP32, (4 rows, 256 threads) / (1, 256) / (1, 1,024): 100 x
+// 60,000 28.6 / 18.9 / 15.4, 20.6 / 9.9 / 9.3; 300 x 60,000 31.0 / 28.8 / 32.2,
+// 27.7 / 17.4 / 19.6; 100 x 20,001 (by element) FP32 10.0 / 8.9 / 7.8; 300 x 16,000 12.6 / 11.0 / 12.6; 1,000 x 514 7.9 / 7.9 / 10.4
+// (the call's own 7.7); 1,000 x 16,000 22.5 / 23.0 / 26.4; 2,500 x 2,048 9.8 / 11.5 /
+// 19.6; 5,000 x 16,000 109 / 122 / 134; 20,000 x 514 19.4 / 30.5 / 86.6.
+struct RowPass {
+    int u, bs;
+};
+RowPass row_pass(const DenseView& d) {
+    if (d.rows >= 1024) return {4, 256};
+    return {1, d.rows <= 128 && d.cols / slice_elems(d) > 12288 ? 1024 : 256};
+}
+
+template <typename T, int VN, bool XA>
 hipError_t launch_rows_vn(const DenseView& d, const T* x, const double* fbar, double* partials,
                           double* v, int groups, hipStream_t s) {
-    // Few rows: one to a wide workgroup, so that more of the device reads;
-    // many: four at a time, which share the loads of x.
-    if (d.rows < 1024)
-        PG_LAUNCH((k_dense_rows<T, VN, 1, 1024>), dim3(groups), dim3(1024), 0, s, d, x, fbar,
-                  partials, v);
+    const RowPass r = row_pass(d);
+    const dim3 grid(groups), block(r.bs);
+    if (r.u == 4)
+        PG_LAUNCH((k_dense_rows<T, VN, 4, 256, XA>), grid, block, 0, s, d, x, fbar, partials, v);
+    else if (r.bs == 256)
+        PG_LAUNCH((k_dense_rows<T, VN, 1, 256, XA>), grid, block, 0, s, d, x, fbar, partials, v);
     else
-        PG_LAUNCH((k_dense_rows<T, VN, 4, 256>), dim3(groups), dim3(256), 0, s, d, x, fbar,
-                  partials, v);
+        PG_LAUNCH((k_dense_rows<T, VN, 1, 1024, XA>), grid, block, 0, s, d, x, fbar, partials, v);
     return hipGetLastError();
 }
 
@@ -640,9 +664,14 @@ hipError_t launch_rows_t(const DenseView& d, const void* x, const double* fbar, 
                          double* v, int groups, hipStream_t s) {
     constexpr int VN = 16 / sizeof(T);
     const T* xp = static_cast<const T*>(x);
-    if (slice_elems(d) == VN && (uintptr_t)x % 16 == 0)
-        return launch_rows_vn<T, VN>(d, xp, fbar, partials, v, groups, s);
-    return launch_rows_vn<T, 1>(d, xp, fbar, partials, v, groups, s);
+    if (slice_elems(d) != VN) return launch_rows_vn<T, 1, true>(d, xp, fbar, partials, v, groups, s);
+    if ((uintptr_t)x % 16 == 0) return launch_rows_vn<T, VN, true>(d, xp, fbar, partials, v, groups, s);
+    // x off the 16-byte grid; A by slice / by element, us: FP64 1,025 x 16,000 25.5 /
+    // 30.3, 2,500 x 30,000 109 / 116; FP32 500 x 16,000 9.5 / 11.6, but 5,000 x
+    // 16,000 57 / 53, 1,025 x 12,000 13.9 / 12.8.
+    if (sizeof(T) == 8 || row_pass(d).u == 1)
+        return launch_rows_vn<T, VN, false>(d, xp, fbar, partials, v, groups, s);
+    return launch_rows_vn<T, 1, true>(d, xp, fbar, partials, v, groups, s);
 }
 
 template <typename T>
@@ -690,7 +719,8 @@ DenseCfg dense_config(const DenseView& d) {
         const int64_t chunks = std::max<int64_t>(1, (d.cols / vn + 255) / 256);
         c.bands = (int)std::max<int64_t>(1, std::min<int64_t>(2048 / chunks, d.rows / 8));
     }
-    c.row_groups = (int)std::max<int64_t>(1, std::min<int64_t>(2048, d.rows < 1024 ? d.rows : (d.rows + 3) / 4));
+    const int64_t u = row_pass(d).u;
+    c.row_groups = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (d.rows + u - 1) / u));
     return c;
 }
 
