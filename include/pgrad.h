@@ -320,7 +320,9 @@ typedef struct {
     int32_t block;         /* threads per workgroup of the element pass */
     int32_t tile;          /* elements per thread */
     int32_t lds_slots;     /* LDS table of the combined atomic scatter, or of the
-                              tiled adjoint's corner-round form (0: none; set at bind) */
+                              tiled adjoint's corner-round form (set at bind; 0: none,
+                              also where the bind finds that combining costs more than
+                              it saves, as on random connectivity) */
     int32_t one_launch;    /* 1 if every call is one launch */
     int32_t n_colours;     /* colour classes (colour adjoint, after bind), else 0 */
     int32_t bound;         /* 1 after a successful pg_bind_workspace */

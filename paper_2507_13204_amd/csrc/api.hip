@@ -782,18 +782,29 @@ uint32_t shift_of(const std::vector<std::vector<int32_t>>& tiles) {
 // nodes).  Random meshes, 100,000 rows, FP64 gradient (table / direct, us):
 // rows of four, 14,000 nodes 24.0 / 27.1 (4.6 probes per atomic saved), 20,000
 // nodes 31.6 / 24.6 (6.9); rows of eight, 8,000 nodes 41.9 / 41.7 (3.9), 6,000
-// nodes 55.2 / 51.8 (7.9), 20,000 nodes 69.6 / 42.4 (50).
-bool combining_pays(const std::vector<std::vector<int32_t>>& tiles, int slots, uint32_t shift) {
-    // every eighth sampled workgroup: the sample decides more than it measures
-    int64_t probes = 0, saved = 0;
-    for (size_t i = 0; i < tiles.size(); i += 8) {
-        const int32_t* t = tiles[i].data();
-        const int64_t n = (int64_t)tiles[i].size();
+// nodes 55.2 / 51.8 (7.9), 20,000 nodes 69.6 / 42.4 (50).  And only where a
+// share of the entries worth the table's own work is saved: a ring of 10^6 rows
+// of one 20.0 / 16.6 (none saved), random rows of one, 200,000 on 10,000 nodes
+// 19.3 / 17.6 (2.5%), on 2,000 16.7 / 22.5 (12%), 100,000 rows of three on 10,000
+// nodes 19.6 / 22.5 (7.3%).
+struct Combining {
+    int64_t probes = 0, saved = 0, entries = 0;
+    void add(const std::vector<int32_t>& tile, int slots, uint32_t shift) {
+        const int32_t* t = tile.data();
+        const int64_t n = (int64_t)tile.size();
         int64_t distinct = 0;
         probes += table_cost(&t, &n, 1, slots, shift, INT64_MAX, &distinct);
         saved += n - distinct;
+        entries += n;
     }
-    return probes <= 6 * saved;
+    bool pays(int64_t each) const { return probes <= each * saved && 25 * saved >= entries; }
+};
+
+bool combining_pays(const std::vector<std::vector<int32_t>>& tiles, int slots, uint32_t shift) {
+    Combining c;
+    for (size_t i = 0; i < tiles.size(); i += 8)  // the sample decides more than it measures
+        c.add(tiles[i], slots, shift);
+    return c.pays(6);
 }
 
 void table_of(const std::vector<std::vector<int32_t>>& tiles, int* slots, uint32_t* shift) {
@@ -1145,6 +1156,13 @@ pg_status batch_bind(pg_plan p, hipStream_t s) {
     const int64_t nt = p->batch.n_tiles, ni = (int64_t)p->inst.size();
     if (p->opt.scatter != 1) {
         std::vector<uint32_t> shift((size_t)ni, kHashRotDefault);
+        // Rows of a run-time length combine only where it pays on a tile each
+        // of some eight instances (the fixed lengths always do).  Random rows, 30
+        // instances of 10,000 rows and nodes, FP64 gradient (table / direct, us): rows
+        // of seven 79 / 103 (some seven probes per atomic saved), of ten 156 / 145
+        // (the table full), of 16 280 / 233.
+        Combining c;
+        const int64_t step = (ni + 7) / 8;
         for (int64_t i = 0; i < ni; ++i) {
             const pg_instance& in = p->inst[(size_t)i];
             if (in.n_elems == 0) continue;
@@ -1154,7 +1172,10 @@ pg_status batch_bind(pg_plan p, hipStream_t s) {
                                               tiles, s);
             if (hst != PG_OK) return hst;
             shift[(size_t)i] = shift_of(tiles);
+            if (i % step == 0 && !tiles.empty()) c.add(tiles[tiles.size() / 2], 4096, shift[(size_t)i]);
         }
+        const int32_t k = p->batch.k;
+        p->combine = p->opt.scatter != 0 || k == 2 || k == 4 || k == 8 || c.entries == 0 || c.pays(12);
         for (int64_t t = 0; t < nt; ++t) {
             const int64_t inst = p->h_tiles[(size_t)(4 * t + 3)] >> 40;
             p->h_tiles[(size_t)(4 * t + 2)] =
@@ -1191,7 +1212,7 @@ pg_status batch_run(pg_plan p, const void* x, const double* fbar, void* grad, do
     q.x = x;
     q.partials = p->at<double>(p->o_partials);
     q.block = p->opt.block;
-    q.combine = p->opt.scatter != 1;
+    q.combine = p->opt.scatter != 1 && p->combine;
     q.fbar = fbar;
     if (!grd) {
         q.u_store = t.out ? static_cast<double*>(t.out) : p->at<double>(p->o_u);

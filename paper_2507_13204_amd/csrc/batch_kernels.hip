@@ -161,6 +161,7 @@ hipError_t launch_k(const BatchView& b, const BatchPass& p, hipStream_t s) {
         case 2: return launch_ept<T, 2, MODE>(b, p, s);
         default:
             if (b.tile_elems != p.block) return hipErrorInvalidValue;
+            if (b.k <= 3) return launch_any<T, 3, MODE>(b, p, s);
             if (b.k <= 8) return launch_any<T, 8, MODE>(b, p, s);
             if (b.k <= kAnyRow) return launch_any<T, kAnyRow, MODE>(b, p, s);
             PG_LAUNCH((k_batch_tiles_dyn<T, MODE>), dim3((unsigned)b.n_tiles), dim3(p.block), 0, s, b, p);

@@ -239,6 +239,9 @@ hipError_t launch_elem_dyn_t(const MeshView& m, const MeshPass& p, hipStream_t s
     const int64_t n_items = p.elist ? p.elist_n : m.n_elems;
     const int64_t nb = mesh_blocks(n_items, p.block, 1);
     if (nb == 0) return hipSuccess;
+    // (room for three entries, eight, us: ring of 3 10^6 rows of three, FP64 gradient
+    // 45.1, 49.4, of 10^6 rows of one, objective 11.2, 12.4)
+    if (m.k <= 3) return launch_elem_any<T, 3, MODE>(m, p, nb, s);
     if (m.k <= 8) return launch_elem_any<T, 8, MODE>(m, p, nb, s);
     if (m.k <= kAnyRow) return launch_elem_any<T, kAnyRow, MODE>(m, p, nb, s);
     PG_LAUNCH((k_mesh_elem_dyn<T, MODE>), dim3((unsigned)nb), dim3(p.block), 0, s, m, p);

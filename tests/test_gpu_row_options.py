@@ -87,3 +87,21 @@ def test_batches(k, ckpt, dtype):
         same(obj.objective_tape(x, tape, f_shape=(len(sizes),)))
         obj.objective(2 * x)
         assert rel(obj.adjoint_tape(fbar, tape, x).cpu().numpy(), a_ref) <= tg
+
+
+@pytest.mark.parametrize("k,nodes,elems,table", [(1, 6000, 6000, False), (1, 400, 6000, True), (3, 6000, 6000, True),
+                                                 (16, 30_000, 30_000, False), (10, 900, 20_000, True)])
+def test_combining_rule(k, nodes, elems, table):
+    """Rows that share too few nodes go to memory directly, in one mesh and in
+    a batch; a size the caller fixes is kept."""
+    from paper_2507_13204_amd import MeshBatch, MeshObjective
+    ring = nodes == elems and k < 10
+    m = inputs.ring_mesh(elems, k, seed=2) if ring else inputs.random_mesh(nodes, elems, k, seed=2)
+    conn, B, w, x = mesh_to_dev(m, "f64")
+    f_ref, g_ref = oracle.mesh_gradient(m.n_nodes, m.conn, m.B, m.w, m.x)
+    inst = [(m.n_nodes, m.n_elems, 0, 0)]
+    for scatter in (0, 2):
+        for obj in (MeshObjective(conn, B, w, m.n_nodes, scatter=scatter), MeshBatch(inst, conn, B, w, scatter=scatter)):
+            assert (obj.info()["lds_slots"] > 0) == (table or scatter == 2)
+            f, g = obj.gradient(x)
+            assert srel(f.reshape(-1)[0].item(), f_ref) <= TOL_F64_F and rel(g.cpu().numpy(), g_ref) <= TOL_F64_G
