@@ -591,8 +591,8 @@ SmallPass small_pass(pg_plan p) {
 
 // Lets the element pass sum f itself (through the ticket in the flag words)
 // where its grid is small enough; an empty mesh launches nothing.
-bool sum_in_pass(pg_plan p, MeshPass& q, double* f_out) {
-    if (p->mesh_blocks_n == 0 || p->mesh_blocks_n > kTicketBlocks) return false;
+bool sum_in_pass(pg_plan p, MeshPass& q, double* f_out, int64_t most) {
+    if (p->mesh_blocks_n == 0 || p->mesh_blocks_n > most) return false;
     q.ticket = p->at<int32_t>(p->o_flag) + 2;  // zeroed at bind
     q.f_out = f_out;
     return true;
@@ -639,7 +639,7 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
     }
     if (!grd) {
         q.u_store = t.out ? static_cast<double*>(t.out) : p->at<double>(p->o_u);
-        const bool ticket = f_out && sum_in_pass(p, q, f_out);
+        const bool ticket = f_out && sum_in_pass(p, q, f_out, kTicketObjective);
         PG_HIP(tkern(p, true));
         PG_HIP(launch_mesh_elem(m, M_PRIMAL, q, s));
         PG_HIP(tkern(p, false));
@@ -725,7 +725,7 @@ pg_status mesh_run(pg_plan p, const void* x, const double* fbar, void* grad, dou
             q.gacc = static_cast<double*>(grad);
             if (!acc) PG_HIP(launch_zero(grad, sizeof(double) * (size_t)m.n_nodes, s));
         }
-        const bool ticket = !f32 && obj && f_out && sum_in_pass(p, q, f_out);
+        const bool ticket = !f32 && obj && f_out && sum_in_pass(p, q, f_out, kTicketGradient);
         PG_HIP(tkern(p, true));
         PG_HIP(launch_mesh_elem(m, obj ? M_GRAD_ATOMIC : M_ADJ_ATOMIC, q, s));
         PG_HIP(tkern(p, false));
@@ -1811,7 +1811,7 @@ pg_status pg_jvp(pg_plan p, const void* x, const void* d, double* jvp_out, pg_st
         PG_HIP(launch_mesh_small(p->mesh, M_JVP, q, sp, s));
         return PG_OK;
     }
-    const bool ticket = sum_in_pass(p, q, jvp_out);
+    const bool ticket = sum_in_pass(p, q, jvp_out, kTicketJvp);
     PG_HIP(launch_mesh_elem(p->mesh, M_JVP, q, s));
     if (!ticket) PG_HIP(launch_final_sum(q.partials, p->mesh_blocks_n, jvp_out, s));
     return PG_OK;

@@ -104,9 +104,14 @@ struct MeshPass {
 // Grids up to which the last workgroup sums f: each workgroup waits for its
 // two trips to the coherence point while it holds its place on the compute
 // unit, which costs more than a launch where there are more than fit at once.
-// FP64 gradients (launch / ticket, us): 35 workgroups 11.6 / 9.1, 116 11.2 /
-// 10.1, 203 10.8 / 11.0, 325 12.4 / 13.5, 963 19.4 / 26.1.
-constexpr int64_t kTicketBlocks = 160;
+// The launch is hidden behind the pass as far as the host enqueues in time,
+// which a gradient's longer pass lets it do, an objective's on a quick host
+// only and a JVP's on neither.  FP64 hex meshes, us, launch from a quick host / from
+// a slow one / ticket: gradient 39 workgroups 9.2 / 10.8 / 9.0, 70 - / 9.5 / 9.1, 77
+// 9.2 / 9.7 / 9.4, 99 9.1 / 9.7 / 9.8, 125 9.3 / 9.4 / 10.1; objective 31 6.5 / 7.7 /
+// 5.9, 77 6.5 / 7.4 / 6.4, 99 6.1 / 7.5 / 6.6, 125 6.1 / 7.4 / 6.9, 156 6.4 / 7.9 /
+// 7.5; JVP 125 8.2 / 9.5 / 7.2, 156 - / 9.4 / 7.8.
+constexpr int64_t kTicketGradient = 72, kTicketObjective = 128, kTicketJvp = 160;
 
 // Number of workgroups an element pass over n items launches.
 int64_t mesh_blocks(int64_t n_items, int block, int ept);

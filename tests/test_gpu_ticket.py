@@ -59,3 +59,26 @@ def test_calls_that_overlapped_leave_the_counter_ready(make):
         call(streams[0], g[0], f[0])
         torch.cuda.synchronize()
         assert srel(f[0].item(), want) <= TOL_F64_F
+
+
+@pytest.mark.parametrize("n", [33, 34, 35, 41, 42, 44, 45])
+def test_both_sides_of_the_lines(n):
+    """Grids just below and above those up to which a gradient (72 workgroups),
+    an objective (128) and a JVP (160) sum f themselves, repeated and with f
+    written in place."""
+    from paper_2507_13204_amd import MeshObjective
+    m = inputs.hex_mesh(n, seed=n)
+    f_ref, g_ref = oracle.mesh_gradient(m.n_nodes, m.conn, m.B, m.w, m.x)
+    obj, x = MeshObjective(to_dev(m.conn), to_dev(m.B), to_dev(m.w), m.n_nodes), to_dev(m.x)
+    d = torch.linspace(-1, 1, m.n_nodes, dtype=torch.float64, device="cuda")
+    f = torch.empty((), dtype=torch.float64, device="cuda")
+    j_ref = float(g_ref @ d.cpu().numpy())
+    first = None
+    for _ in range(3):
+        obj.gradient(x, f_out=f)
+        fg = f.clone()
+        fo, j = obj.objective(x), obj.jvp(x, d)
+        assert srel(fg.item(), f_ref) <= TOL_F64_F and srel(j.item(), j_ref) <= 1e-9
+        assert torch.equal(fg, fo)  # the same partials in the same order, summed here or there
+        assert first is None or torch.equal(first, fg)
+        first = fg
