@@ -182,7 +182,11 @@ struct pg_prog_s {
 namespace {
 
 // Incidences of a gather from which its reverse may go through the transposed
-// connectivity (below, the extra launches cost more than the atomics), and up
+// connectivity: where the extra launches cost no more than the atomics whatever
+// the length of a row.  Gradients on half as many entries, atomics / transposed,
+// us: rows of one 32,768 incidences 12.4 / 13.9, 65,536 13.6 / 13.8, 131,072 18.8 /
+// 14.7; rows of four 8,192 10.8 / 13.1, 32,768 15.7 / 13.5; rows of eight 8,192 11.7
+// / 13.7, 16,384 32.6 / 14.2, 65,536 56.8 / 14.7.  And up
 // to which the plan keeps room for it (16 bytes per incidence, 8 of them shared
 // by the program's gathers, and 4 to 32 per entry).
 constexpr int64_t kTransposeMin = 1 << 16, kTransposeMax = 1 << 23;
@@ -201,7 +205,9 @@ constexpr int64_t kPartBytes = 6 << 20;
 // 800,000 on 8 times 63 / 53, 16 70 / 85, 32 87 / 165; 1.6 M on 8 times 148 /
 // 138, 16 190 / 196, 32 256 / 326.
 constexpr int64_t kTransposeEntries = 8;
-// Incidences of one operand entry up to which one thread adds them.
+// Incidences of one operand entry up to which one thread adds them (the most
+// of any entry; 200,000 rows of four on as many entries, atomics / transposed, us:
+// 128 50 / 29, 256 50 / 34, 512 51 / 45, 1,024 51 / 70, 4,096 51 / 221).
 constexpr int32_t kTransposeDegree = 256;
 
 // Sampled workgroups of a gather's scatter: at most kSampled of them, evenly
@@ -221,7 +227,12 @@ hipError_t copy_tile(const Op& op, int64_t q, std::vector<int32_t>* out) {
 
 // Whether the sampled workgroups' scatter (every step-th) into n_nodes entries
 // is one memory request for every fourth incidence or more: a flush instruction
-// costs a request per 128-byte line of its 64 entries.
+// costs a request per 128-byte line of its 64 entries.  200,000 rows of eight
+// on 300,000 entries within a window, atomics / transposed, us: 0.02 lines per
+// incidence 15 / 30 (a structured mesh 14 / 29), 0.04 18 / 31, 0.07 65 / 31, 0.13 72 /
+// 33, 0.25 82 / 34, 0.49 (a mesh in shuffled order) 104 / 33, 0.90 122 / 38: what
+// is transposed gains for certain, what lies between keeps its 16 bytes per
+// incidence.
 bool scattered(const std::vector<std::vector<int32_t>>& tiles, size_t step, int64_t n_nodes) {
     std::vector<uint64_t> seen((size_t)(n_nodes >> 10) + 1, 0);  // one bit per line
     auto in = [&](int32_t n) { return n >= 0 && n < n_nodes; };  // a plan has not checked them yet
