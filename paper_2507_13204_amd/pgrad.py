@@ -717,6 +717,8 @@ class Program:
         off = (-raw.data_ptr()) % WORKSPACE_ALIGN
         self._ws_raw = raw
         self._ws = raw[off:off + sz.value]
+        # the bind works on the null stream: whatever used this memory before has ended
+        torch.cuda.synchronize(device)
         check(lib().pg_prog_bind_workspace(self._p, ctypes.c_void_p(self._ws.data_ptr()),
                                            sz.value), "pg_prog_bind_workspace")
         return self
