@@ -269,7 +269,7 @@ bool may_be_scattered(const Op& op, int64_t n_nodes) {
 }
 
 // Gathers whose connectivity a run found changed go back to atomics from the
-// first run (or query) after that one has ended.  Until then, and in a graph
+// first run after that one has ended.  Until then, and in a graph
 // captured before, the launches see to it on the device, which scatters without
 // combining.  Random rows of eight, then random ones again and then structured
 // ones, a gradient in transposed order / changed to random, by the device / with
@@ -277,14 +277,18 @@ bool may_be_scattered(const Op& op, int64_t n_nodes) {
 // 200,003 rows on 300,007 entries 38 / 104 / 121 / 40 / 16; 10^6 on 10^6 251 /
 // 562 / 421 / 182 / 34; 100,000 on 100,000 24 / 53 / 81 / 22 / 14.  (With
 // atomics from the start 125, 422 and 93 random, 15, 35 and 14 structured.)
+bool found_changed(const Group& g) { return g.transposed && g.word >= 0 && HostWords::get().is_set(g.word); }
+void count_changed(pg_prog_stats* st) {
+    ++st->atomic_ops;
+    --st->rescheduled_ops;
+    st->rev_kernels -= 2;
+}
 void settle_changed(pg_prog p) {
     for (Group& g : p->groups) {
-        if (!g.transposed || g.word < 0 || !HostWords::get().is_set(g.word)) continue;
+        if (!found_changed(g)) continue;
         g.transposed = false;
         p->stored_first[(size_t)p->ops[(size_t)g.gather].a] = 0;
-        ++p->stats.atomic_ops;
-        --p->stats.rescheduled_ops;
-        p->stats.rev_kernels -= 2;
+        count_changed(&p->stats);
     }
 }
 
@@ -1173,8 +1177,9 @@ pg_status pg_prog_info(pg_prog p, pg_prog_stats* stats) {
     clear_error();
     if (!p || !stats) return perr(PG_EINVAL, "NULL argument");
     if (!p->planned) return perr(PG_ESTATE, "call pg_prog_plan first");
-    settle_changed(p);
     *stats = p->stats;
+    for (const Group& g : p->groups)  // what the next run will settle
+        if (found_changed(g)) count_changed(stats);
     return PG_OK;
 }
 
