@@ -83,8 +83,8 @@ HEX_KERNELS = {
 
 def _f32_peak(m: int, n: int) -> float:
     """TFLOP/s of the unit that the FP32 products of this size run on: the FP32
-    matrix instruction, or (from 2^20 entries) six bfloat16 products for each."""
-    return 157.3 if m * n < 1 << 20 else round(2500 / 6, 1)
+    matrix instruction, or (from 2^20 entries and 256 rows) eight bfloat16 products for each."""
+    return 157.3 if m * n < 1 << 20 or m < 256 else round(2500 / 8, 1)
 
 
 def traffic_record(kernel_key: str):
@@ -522,7 +522,7 @@ def _other_configs(args):
         k_f = _hook_ms(o, lambda: o.objective(X), steps)
         res[f"bdense_{dt}"] = {
             "workload": f"batched dense A {m_}x{m_}, X {m_}x{n_}, {dt} matrix cores"
-                        + (", operands in three bfloat16 parts, each 32-deep k-step added into FP64" if dt == "f32" else ""),
+                        + (", operands in three bfloat16 parts, eight products each, added into FP64" if dt == "f32" else ""),
             "forward_kernel_ms": round(k_f, 5),
             "forward_TFLOPs": round(flop / (k_f * 1e-3) / 1e12, 3),
             "forward_frac_peak": round(flop / (k_f * 1e-3) / 1e12 / peak, 4),

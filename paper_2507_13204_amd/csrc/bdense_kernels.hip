@@ -169,7 +169,7 @@ struct Frag {
 // Bound by the matrix cores in FP64 (67 TFLOP/s of 78.6 at 4096 x 1024, 59 with
 // the tiles staged through LDS and a barrier per k-step), by the vector
 // instructions of the split and the FP64 sums, beside the eight products, in
-// FP32 (4,096 x 1,024: 530-554 us a gradient, 127 TFLOP/s; 1,323 on
+// FP32 (4,096 x 1,024: 530-580 us a gradient, 118-130 TFLOP/s; 1,323 on
 // v_mfma_f32_16x16x4_f32; six products in one sum, which was less accurate, 456),
 // and by latency below some 500 x 500: 257 x 129 takes 10.6 us per FP32 gradient.
 template <typename T, int AR, bool TRANS_A, int EPI, typename S>
